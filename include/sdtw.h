@@ -251,16 +251,23 @@ int sdtw_free_reference(sdtw_ref ref);
 
 /*
  * Validate and schedule a batch layout once; reuse it for every batch with
- * the same read lengths.  Reads are ordered longest first and pulled by a
- * persistent grid (one launch per group of reads that share a kernel
- * configuration); reads of 64 rows or fewer go to the one-wave kernel.
+ * the same read lengths.  Reads of up to 2,048 rows share waves that hold a
+ * few rows of them per lane, and the reference is cut into column segments
+ * that are aligned at once, as many as a cost model of the launch finds best
+ * for the batch and the reference's length.  Longer reads, and every read of
+ * a plan whose launch shape was set (sdtw_plan_set_config), run on the
+ * column-lane kernels: ordered longest first and pulled by a persistent grid
+ * (one launch per group of reads that share a kernel configuration), reads of
+ * 64 rows or fewer by the one-wave kernel.
  *
  *   offsets_host  int64[nq+1] CSR offsets of the query values, read r is
  *                 q[offsets[r] .. offsets[r+1]); every read 1 <= M <=
  *                 SDTW_MAX_QUERY (EINVAL otherwise).
  *   nq            >= 1.
  *   dtype         SDTW_F32 or SDTW_I16 (the query dtype of later calls).
- *   out           receives the plan (device memory is allocated here).
+ *   out           receives the plan (device memory is allocated here: the
+ *                 layout and the segments' scratch, a few MB to about 140 MB
+ *                 for large batches of long reads).
  */
 int sdtw_plan_create(const int64_t* offsets_host, int32_t nq, int dtype,
                      sdtw_plan* out);
@@ -269,8 +276,9 @@ int sdtw_plan_create(const int64_t* offsets_host, int32_t nq, int dtype,
 int sdtw_plan_info(sdtw_plan plan, int32_t* nq, int* dtype, int32_t* max_m);
 
 /*
- * Override the kernel configuration chosen for a plan (autotuning).  Results
- * never depend on it.
+ * Override the kernel configuration chosen for a plan: its reads then run on
+ * the column-lane kernels in this shape (sdtw_plan_autotune and
+ * sdtw_plan_use_tuned give the choice back).  Results never depend on it.
  *   strip   columns per lane: 8, 16 or 32 (0 = keep).
  *   chains  independent dependency chains per lane for long reads: 1, 2 or
  *           4 (0 = keep); strip / chains must be a multiple of 4.  Reads
@@ -300,8 +308,9 @@ int sdtw_plan_get_config(sdtw_plan plan, int* strip, int* chains, int* bands,
                          int* waves_per_cu, int32_t* band_rows);
 
 /*
- * Autotune the plan's kernel configuration on this batch: run every
- * candidate (strip 16 or 32, 1 or 2 chains, 1 to 4 bands where valid,
+ * Autotune the plan's kernel configuration on this batch.  Reads of up to
+ * 2,048 rows need none (see sdtw_plan_create); if the plan has longer ones, run
+ * every candidate (strip 16 or 32, 1 or 2 chains, 1 to 4 bands where valid,
  * with 3 or 4 bands also band_rows targets of a half and a third of the
  * median read, each at the waves per CU its LDS allows and at half that)
  * in two passes (the second in reverse order), each a warm-up launch and one
@@ -362,21 +371,27 @@ int sdtw_align_one(sdtw_ref ref, const void* q_dev, int32_t M, void* cost_dev,
                    int32_t* end_dev, void* stream);
 
 /*
- * One read spread over every compute unit (int16 references only): each of
- * the M rows of Eq. 1 is computed as a prefix scan over the N columns (a row
- * of the recurrence is a composition of maps x -> min(a, x + d), section 4.3
- * computes the same cells as an oblique wavefront), with tiles of 256 x
- * `cols` columns that pass their boundary values to the right through
- * device-memory flags.  Results equal sdtw_align_one's bit for bit; the
- * latency no longer grows with N / (columns of one workgroup).
+ * One read spread over every compute unit (int16 references only).  Results
+ * equal sdtw_align_one's bit for bit; the latency no longer grows with N /
+ * (columns of one workgroup).  Reads of up to 2,048 rows with cols = 0 are
+ * aligned against many column segments at once; longer reads, any other
+ * `cols`, and references of 2^20 columns and more on which most segments'
+ * left columns depend on everything to their left (references without
+ * variation) by row scans: each of the M rows of Eq. 1 is computed as a prefix
+ * scan over the N columns (a row of the recurrence is a composition of maps
+ * x -> min(a, x + d), section 4.3 computes the same cells as an oblique
+ * wavefront), with tiles of 256 x `cols` columns that pass their boundary
+ * values to the right through device-memory flags.
  *   q_dev  M int16 values; 1 <= M <= SDTW_MAX_QUERY.
- *   cols   columns per thread, 8, 16, 32 or 64; 0 = the fewest that cut the
- *          reference into at most 64 tiles, else into at most 256, else 32
- *          (the fastest choice measured for each reference length).
+ *   cols   columns per thread of the row scan, 8, 16, 32 or 64; 0 = automatic
+ *          (where the row scan runs, the fewest that cut the reference into at
+ *          most 64 tiles, else into at most 256, else 32: the fastest choice
+ *          measured for each reference length).
  *   cost_dev  out int32[1]; end_dev out int32[1] (0-based column).
- * Enqueues three kernels and records an event that tracks the reuse of its
- * library-owned scratch (8 bytes per tile per row: 8 MiB per call in flight
- * unless more is needed), so the call is not for graph capture.  If a
+ * Enqueues two to five kernels and records an event that tracks the reuse of
+ * its library-owned scratch (8 MiB per call in flight unless more is needed:
+ * 8 bytes per tile per row for the row scan, 4 bytes per row and segment), so
+ * the call is not for graph capture.  If a
  * tile waits for its left neighbour for about a second (a defect; never in
  * normal operation) every wait ends and cost and end are -1.
  * EINVAL for a float32 reference.
@@ -392,7 +407,7 @@ int sdtw_align_one_wide(sdtw_ref ref, const void* q_dev, int32_t M, int cols, vo
  * device it runs on until the process ends, and the call records no event.
  * It calls no hipMalloc, hipFree or allocating routine; the first call on a
  * device looks the array's address up once.
- *   Limit: wide scratch words = 2 M t + M ceil(t / 64) + t + 1 for t =
+ *   Limit, whichever way the read is aligned: 2 M t + M ceil(t / 64) + t + 1 for t =
  *   ceil(N / (256 cols)) tiles must not exceed 2^20 (EINVAL otherwise, with
  *   the sizes in the message; nothing is launched).  For example M = 250
  *   fits up to about 16 M columns at cols = 32.
@@ -466,10 +481,11 @@ int sdtw_stream_copy_row(sdtw_stream s, void* dst_dev, void* stream);
  * and 0-based end of the new last row (as sdtw_align_batch).  A stream's
  * row count advances when the call returns; calls on the same streams must
  * be issued in order on one HIP stream (or ordered by the caller).  Calls
- * on other streams may run at once on other HIP streams: against
- * references of 2^20 columns or more two calls' workgroups share a CU once
- * the calls in flight (the library counts its own) cover more than half
- * the CUs, and take CUs of their own below that.  Placement never changes
+ * on other streams may run at once on other HIP streams; their workgroups
+ * share CUs.  (With a launch shape set, and for chunks of more than 2,048 rows,
+ * two calls' workgroups against references of 2^20 columns or more share a
+ * CU once the calls in flight, the library counts its own, cover more than half
+ * the CUs, and take CUs of their own below that.)  Placement never changes
  * results.
  */
 int sdtw_stream_extend(const sdtw_stream* streams, int32_t ns, const void* chunk_dev,
@@ -478,9 +494,8 @@ int sdtw_stream_extend(const sdtw_stream* streams, int32_t ns, const void* chunk
 
 /*
  * Extend one stream by one chunk over the whole device (section 2.2's
- * per-chunk decision, Eq. 1 continued from the resident row): the chunk's
- * rows as row scans across tiles of 256 x cols columns, as
- * sdtw_align_one_wide does for a whole read, starting from the stream's
+ * per-chunk decision, Eq. 1 continued from the resident row), as
+ * sdtw_align_one_wide does a whole read, starting from the stream's
  * resident row and writing the new last row back over it.  For a few
  * chunks against a long reference, whose batched extension is bounded by
  * one chunk's four waves, this answers in milliseconds; it uses the whole
@@ -525,13 +540,14 @@ int sdtw_stream_best_two(const sdtw_stream* streams, int32_t ns, int32_t window,
 
 /*
  * Launch shape of later sdtw_stream_extend calls on streams of `ref` (one
- * chain per lane); ref = NULL sets the process default that references
- * without their own setting use.
- *   strip  columns per lane, 16 or 32; 0 (default) = 32 for references of
- *          2^20 columns or more, else 16.
+ * chain per lane of the column-lane kernel); ref = NULL sets the process
+ * default that references without their own setting use.  With both 0 (the
+ * default) chunks of up to 2,048 rows are laid out as sdtw_plan_create does.
+ *   strip  columns per lane, 16 or 32; 0 = 32 for references of 2^20 columns
+ *          or more, else 16.
  *   bands  waves per chunk (the row bands of sdtw_plan_set_config), 1 to 4;
- *          0 (default) = 4 for at most two chunks per compute unit, 2 for
- *          at most four, else 1 (a chunk of M rows uses at most M / 65).
+ *          0 = 4 for at most two chunks per compute unit, 2 for at most four,
+ *          else 1 (a chunk of M rows uses at most M / 65).
  * Results never depend on it.  EINVAL for other values.
  */
 int sdtw_stream_set_config(sdtw_ref ref, int strip, int bands);

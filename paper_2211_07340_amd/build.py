@@ -4,11 +4,14 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libsdtw.so")
-SOURCES = ["api.hip", "prep.hip", "align.hip", "scores.hip", "wide.hip", "events.hip"]
+SOURCES = ["rows_i16.hip", "rows_f32.hip", "rows_i16_stream.hip", "rows_f32_stream.hip",
+           "align.hip", "api.hip", "prep.hip", "scores.hip", "wide.hip", "events.hip"]
 ARCH = os.environ.get("SDTW_OFFLOAD_ARCH", "gfx950")
 
 FLAGS = [
@@ -42,17 +45,32 @@ def build_probe(verbose: bool = False) -> str:
     return PROBE_LIB
 
 
-def build(verbose: bool = False, save_temps: str | None = None) -> str:
+def _compile(src: str, obj: str, save_temps: str | None):
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    cmd = [hipcc, *FLAGS, "-o", LIB + ".tmp", *[os.path.join(CSRC, s) for s in SOURCES]]
+    cmd = [hipcc, *[f for f in FLAGS if f != "-shared"], "-c", "-o", obj,
+           os.path.join(CSRC, src)]
     if save_temps:
-        os.makedirs(save_temps, exist_ok=True)
-        cmd.insert(1, f"-save-temps={'obj'}")
-    proc = subprocess.run(cmd, capture_output=True, text=True, cwd=save_temps or HERE)
-    out = "\n".join(l for l in (proc.stdout + proc.stderr).splitlines()
+        cmd.insert(1, "-save-temps=obj")
+    return subprocess.run(cmd, capture_output=True, text=True, cwd=HERE)
+
+
+def build(verbose: bool = False, save_temps: str | None = None) -> str:
+    """Compile the sources side by side and link them."""
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    workers = int(os.environ.get("MAX_JOBS", "0")) or min(len(SOURCES), os.cpu_count() or 1)
+    with tempfile.TemporaryDirectory() as tmp, ThreadPoolExecutor(workers) as pool:
+        into = save_temps or tmp
+        os.makedirs(into, exist_ok=True)
+        objs = [os.path.join(into, s + ".o") for s in SOURCES]
+        done = list(pool.map(_compile, SOURCES, objs, [save_temps] * len(SOURCES)))
+        if all(p.returncode == 0 for p in done):
+            done.append(subprocess.run([hipcc, *FLAGS, "-o", LIB + ".tmp", *objs],
+                                       capture_output=True, text=True, cwd=HERE))
+    out = "\n".join(l for p in done for l in (p.stdout + p.stderr).splitlines()
                     if "packed-fp32-ops" not in l)
-    if proc.returncode != 0:
-        raise RuntimeError(f"hipcc failed ({proc.returncode}):\n{out}")
+    bad = [p.returncode for p in done if p.returncode != 0]
+    if bad:
+        raise RuntimeError(f"hipcc failed ({bad[0]}):\n{out}")
     if verbose and out.strip():
         print(out, file=sys.stderr)
     os.replace(LIB + ".tmp", LIB)

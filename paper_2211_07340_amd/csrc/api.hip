@@ -48,6 +48,10 @@ struct sdtw_stream_s {
   std::shared_ptr<sdtw::CallToken> last;  // last extend that used the row
 };
 
+namespace sdtw {
+struct RowLayout;
+}
+
 struct sdtw_plan_s {
   int device;
   int dtype;
@@ -63,6 +67,16 @@ struct sdtw_plan_s {
   int32_t band_rows;              // target rows per band (0: as many bands as fit)
   int waves_per_cu;               // persistent grid density (bands x workgroups per CU)
   int cus;                        // compute units of the device
+  // Row-lane kernel (rows.h), for the reads of up to kRowsMaxM rows: order[nlong ..)
+  bool rows;                      // use it (a launch shape set by the caller: the skew kernel)
+  int32_t nlong;                  // reads too long for it
+  sdtw::RowLayout* lay[2];        // reads sharing waves; reads alone in theirs
+  sdtw::RowPack* packs_dev[2];
+  int64_t scratch_words;
+  uint64_t* scratch;
+  int64_t cut_n;                  // reference length that `cut` is for (0: none yet)
+  int cut_lay;
+  sdtw::RowsArgs cut;             // how it is cut
 };
 
 namespace sdtw {
@@ -115,6 +129,228 @@ static int cu_count() {
   return v;
 }
 
+
+// ---- row-lane kernel: packs and segments -----------------------------------
+
+// Reads on the lanes of waves: packs class by class (rows per lane), most
+// rows per lane first.
+struct RowLayout {
+  std::vector<RowPack> packs;
+  std::vector<RowClass> classes;
+};
+
+// Rows per lane of a read that shares waves with reads like it: those that
+// leave the smallest share of the lanes' work to idle lanes and to what a
+// step does besides cells (about 1.5 instructions a column against 2 R).
+static int rows_to_share(int32_t m, int max_reads) {
+  int best = 0;
+  double most = 0.0;
+  for (int R : kRowsPerLane) {
+    const int32_t lanes = rows_lanes(m, R);
+    if (!lanes) continue;
+    const int32_t reads = std::min<int32_t>(max_reads, kLanes / lanes);
+    const double part = (double)reads * m / (kLanes * (R + 0.2));
+    if (part > most) {
+      most = part;
+      best = R;
+    }
+  }
+  return best;
+}
+// Rows per lane of a read alone in its wave: the fewest (the shortest steps).
+static int rows_alone(int32_t m) {
+  for (int R : {2, 4, 8, 16, 32})
+    if (rows_lanes(m, R)) return R;
+  return 0;
+}
+
+// Packs of the reads (item, rows), longest first.  `alone`: a read per pack;
+// else reads of the same rows per lane share a wave while their lanes fit,
+// each pack filled with the longest that still fit.
+static RowLayout rows_layout(const std::vector<std::pair<int32_t, int32_t>>& reads, bool alone,
+                             int max_reads) {
+  RowLayout out;
+  std::vector<int> rows(reads.size());
+  for (size_t i = 0; i < reads.size(); ++i)
+    rows[i] = alone ? rows_alone(reads[i].second) : rows_to_share(reads[i].second, max_reads);
+  if (alone) max_reads = 1;
+  for (int k = kRowsClasses - 1; k >= 0; --k) {
+    const int R = kRowsPerLane[k];
+    // by lanes: the reads that take that many, longest last
+    std::vector<std::vector<std::pair<int32_t, int32_t>>> by(kLanes + 1);
+    for (size_t i = reads.size(); i-- > 0;)
+      if (rows[i] == R) by[rows_lanes(reads[i].second, R)].push_back(reads[i]);
+    RowClass c{};
+    c.rows_per_lane = R;
+    c.first_pack = (int32_t)out.packs.size();
+    for (int top = kLanes; top >= 1;) {
+      if (by[top].empty()) {
+        --top;
+        continue;
+      }
+      RowPack p{};
+      int32_t room = kLanes;
+      while (p.nreads < max_reads && room > 0) {
+        int l = std::min(room, top);
+        while (l >= 1 && by[l].empty()) --l;
+        if (l < 1) break;
+        const auto rd = by[l].back();
+        by[l].pop_back();
+        p.item[p.nreads] = rd.first;
+        p.lane0[p.nreads] = kLanes - room;
+        ++p.nreads;
+        room -= l;
+        p.max_lanes = std::max(p.max_lanes, (int32_t)l);
+        p.max_m = std::max(p.max_m, rd.second);
+      }
+      for (int j = p.nreads; j <= kRowsReads; ++j) p.lane0[j] = kLanes - room;
+      c.max_m = std::max(c.max_m, p.max_m);
+      c.max_lanes = std::max(c.max_lanes, p.max_lanes);
+      out.packs.push_back(p);
+    }
+    c.npacks = (int32_t)out.packs.size() - c.first_pack;
+    if (c.npacks) out.classes.push_back(c);
+  }
+  return out;
+}
+
+// The time of a launch in cycles, by a model of the sweep and the halo
+// kernel.  A SIMD issues one of a step's instructions (8 R for the cells, on
+// float32 counted as if it had two per cell, and a few more) per `cycles`,
+// by the waves on it: measured on the sweep at 16 rows per lane (4,096 reads
+// of 250 rows x 59,796 columns, 1,024 waves per round) and, alike, on bare
+// v_min3_u32 and v_sad_u32 (6.2, 5.05 and 4.55 with one, two and four
+// waves).  Rows handed on through LDS, a lone wave waits for the round trip
+// (about 420 cycles), and four LDS operations a step of 8 to 10 cycles for
+// each of the CU's four SIMDs bound the narrowest packs (240 cycles a step at
+// 4 rows per lane with three waves, 190 with four).
+struct RowCost {
+  bool dpp, f32;
+  double step(int R, double rounds) const {  // of all of a SIMD's waves
+    static const double kI16[] = {6.2, 6.2, 5.05, 4.7, 4.5}, kF32[] = {6.0, 6.0, 4.4, 4.75, 4.25};
+    const double ops = 8.0 * R + (dpp ? 10.0 : 2.0);
+    const double cycles = (f32 ? kF32 : kI16)[(int)std::min(rounds, 4.0)];
+    const double wave = std::max(ops * cycles, dpp ? 0.0 : (rounds < 4.0 ? 240.0 : 190.0));
+    return std::max(rounds * wave, (dpp ? 0.0 : 420.0) + 6.2 * ops);
+  }
+};
+
+// Most waves of a SIMD a launch is cut into, one after another or at once:
+// the bound of the scratch that its boundary columns need.
+constexpr int kRowsRounds[] = {1, 2, 3, 4, 6, 8, 12, 16};
+
+// Cuts the reference of n columns into segments for every class so that each
+// SIMD gets `rounds` waves of about equal work (or as many as there are
+// packs for); fills a's counts.  Returns the modelled cycles; *words: the
+// scratch (64-bit words) needed.
+static double rows_cut(RowsArgs& a, const RowLayout& lay, int64_t n, double rounds, RowCost cost,
+                       bool stream, int64_t* words) {
+  const int64_t room = (int64_t)(a.cus * 4 * rounds);
+  auto columns = [&](const RowClass& c, double tau) {  // a segment's, for waves of tau instructions
+    const double cols = 4.0 * tau / (8.0 * c.rows_per_lane + 2.0);
+    const int64_t least = std::max<int64_t>(64, c.max_m / 4);
+    const int64_t whole = (n + 63) & ~(int64_t)63;
+    return std::min(whole, (std::max(least, (int64_t)std::min(cols, 2e9)) + 63) & ~(int64_t)63);
+  };
+  auto count = [&](double tau) {
+    int64_t w = 0;
+    for (const RowClass& c : lay.classes) {
+      const int64_t cols = columns(c, tau);
+      w += c.npacks * ((n + cols - 1) / cols);
+    }
+    return w;
+  };
+  // the shortest waves that the SIMDs have room for
+  double lo = 0.0, hi = 4.0 * (double)n * 300.0;
+  for (int i = 0; i < 40 && count(lo) > room && hi - lo > 4e-3 * hi; ++i) {
+    const double mid = 0.5 * (lo + hi);
+    (count(mid) > room ? lo : hi) = mid;
+  }
+  const double tau = count(lo) > room ? hi : lo;
+  a.nclasses = (int32_t)lay.classes.size();
+  a.nwaves = a.nhalo = 0;
+  int64_t bound = 0, results = 0;
+  for (int k = 0; k < a.nclasses; ++k) {
+    RowClass c = lay.classes[(size_t)k];
+    const int64_t cols = columns(c, tau), s = (n + cols - 1) / cols;
+    c.nseg = (int32_t)s;
+    c.segcols = (int32_t)cols;
+    c.first_wave = a.nwaves;
+    c.first_halo = a.nhalo;
+    c.bound_at = bound;
+    c.result_at = results;
+    a.nwaves += (int32_t)(s * c.npacks);
+    a.nhalo += (int32_t)((s - 1) * c.npacks);
+    if (s > 1) {
+      bound += (s - 1) * c.npacks * rows_bound_words(c.rows_per_lane);
+      results += (int64_t)c.npacks * (stream ? kRowsStreamReads : kRowsReads) *
+                 (rows_groups((int32_t)s) + 1);
+    }
+    a.cls[k] = c;
+  }
+  a.nresults = results;
+  *words = a.nhalo ? results + (results + 1) / 2 + ((int64_t)a.nwaves + 1) / 2 + (bound + 1) / 2
+                   : 0;
+  // The sweep: waves of one class are equally long, so SIMDs that hold fewer
+  // of them wait for the others; of several classes the shorter fill the gaps
+  // but the last.  A launch takes about 8 us besides its steps.
+  const double simds = 4.0 * a.cus, per = a.nwaves / simds;
+  double work = 0.0, longest = 0.0, halo = 0.0;
+  for (int k = 0; k < a.nclasses; ++k) {
+    const RowClass& c = a.cls[k];
+    const double steps = c.segcols / 4.0 + c.max_lanes;
+    const double wave = steps * cost.step(c.rows_per_lane, std::ceil(per)) / std::ceil(per);
+    work += wave * (double)c.nseg * c.npacks / simds;
+    longest = std::max(longest, wave);
+    if (c.nseg > 1) {
+      const double h = ((stream ? 1.33 : 1.125) * c.max_m + 64.0) / 4.0 + c.max_lanes;
+      const double rounds = 2.0 * a.nhalo / simds;
+      // (its steps are guarded one by one: measured 474 cycles at 8 rows per lane
+      // through LDS, 380 with register moves, 1.6 and 1.15 times a sweep's)
+      halo += h * (double)(c.nseg - 1) * c.npacks / a.nhalo * (cost.dpp ? 1.15 : 1.6) *
+              (rounds > 1.0 ? rounds / std::ceil(rounds) : 1.0) *
+              cost.step(c.rows_per_lane, std::ceil(rounds));
+    }
+  }
+  const double sweep = per > 4.0 ? work + 0.5 * longest : std::max(work, longest * std::ceil(per));
+  return sweep + halo + (a.nhalo ? 40000.0 : 20000.0);
+}
+
+// The best of the cuts with scratch of at most most_words words (its modelled
+// cycles, or -1 if none has), and whether to hand rows on in registers (packs
+// of one read, `alone`).
+static double rows_best_cut(RowsArgs& a, const RowLayout& lay, bool alone, int64_t n, bool f32,
+                            bool stream, int64_t most_words, int64_t* words) {
+  double best = -1.0;
+  RowsArgs at = a;
+  for (int dpp = 0; dpp <= (alone ? 1 : 0); ++dpp) {
+    for (int rounds : kRowsRounds) {
+      int64_t w = 0;
+      const double t = rows_cut(at, lay, n, rounds, RowCost{dpp != 0, f32}, stream, &w);
+      if (w > most_words && at.nhalo) continue;
+      if (best < 0.0 || t < best) {
+        best = t;
+        a.nclasses = at.nclasses;
+        a.nwaves = at.nwaves;
+        a.nhalo = at.nhalo;
+        a.nresults = at.nresults;
+        std::copy(at.cls, at.cls + kRowsClasses, a.cls);
+        a.dpp = dpp;
+        *words = w;
+      }
+    }
+  }
+  return best;
+}
+// The parts of the scratch of a cut launch.
+static void rows_scratch(RowsArgs& a, uint64_t* s) {
+  if (!a.nhalo) return;
+  a.keys = s;
+  a.done = (uint32_t*)(s + a.nresults);
+  a.fail = (uint32_t*)(s + a.nresults + (a.nresults + 1) / 2);
+  a.bound = a.fail + (((int64_t)a.nwaves + 1) & ~(int64_t)1);
+}
+
 static bool valid_strip(int s) { return s == 8 || s == 16 || s == 32; }
 
 }  // namespace sdtw
@@ -163,8 +399,13 @@ static RowPool* pool_for(int dev) {
 // ---- pinned descriptor slots for stream_extend -----------------------------
 struct DescSlot {
   StreamItem* host = nullptr;
-  StreamItem* dev = nullptr;  // cap items, then one int32 work counter
+  StreamItem* dev = nullptr;  // cap items, as many packs, then one int32 work counter
   int32_t cap = 0;
+  // (on the host likewise: the packs follow cap items)
+  static constexpr size_t kPer = sizeof(StreamItem) + sizeof(RowPack);
+  RowPack* host_packs() { return (RowPack*)(host + cap); }
+  RowPack* dev_packs() { return (RowPack*)(dev + cap); }
+  int32_t* counter() { return (int32_t*)((char*)dev + kPer * (size_t)cap); }
   uint64_t* part = nullptr;  // sdtw_stream_best_two: per-segment minima
   int64_t part_cap = 0;
   std::shared_ptr<CallToken> last;
@@ -193,10 +434,10 @@ static int ensure_slot(DescSlot& sl, int32_t n) {
   sl.host = nullptr;
   sl.dev = nullptr;
   sl.cap = 0;
-  int rc = check_hip(hipHostMalloc((void**)&sl.host, sizeof(StreamItem) * (size_t)cap),
+  int rc = check_hip(hipHostMalloc((void**)&sl.host, DescSlot::kPer * (size_t)cap),
                      "sdtw_stream_extend: pinned descriptors");
   if (!rc)
-    rc = check_hip(hipMalloc((void**)&sl.dev, sizeof(StreamItem) * (size_t)cap + 64),
+    rc = check_hip(hipMalloc((void**)&sl.dev, DescSlot::kPer * (size_t)cap + 64),
                    "sdtw_stream_extend: device descriptors");
   if (rc) return rc;
   sl.cap = cap;
@@ -456,7 +697,7 @@ struct LaunchGroup {
 static std::vector<LaunchGroup> launch_groups(const sdtw_plan_s* p) {
   std::vector<LaunchGroup> g;
   int32_t pos = 0;
-  const int32_t n = p->nq;
+  const int32_t n = p->rows ? p->nlong : p->nq;  // the rest: the row-lane kernel
   for (int k = p->chains; k >= 1; k /= 2) {
     if (!valid_strip_chains(p->strip, k)) continue;
     const int bands = valid_skew_config(p->strip, k, p->bands) ? p->bands : 1;
@@ -531,6 +772,20 @@ static void choose_config(sdtw_plan_s* p) {
                                                skew_min_m(p->chains)));
 }
 
+// Frees a plan and what it holds; the first error.
+static hipError_t plan_free(sdtw_plan_s* p) {
+  hipError_t first = hipSuccess;
+  for (void* d : {(void*)p->offs_dev, (void*)p->order_dev, (void*)p->sched_dev,
+                  (void*)p->packs_dev[0], (void*)p->packs_dev[1], (void*)p->scratch}) {
+    const hipError_t e = hipFree(d);
+    if (first == hipSuccess) first = e;
+  }
+  delete p->lay[0];
+  delete p->lay[1];
+  delete p;
+  return first;
+}
+
 int sdtw_plan_create(const int64_t* offsets_host, int32_t nq, int dtype, sdtw_plan* out) {
   SDTW_REQUIRE(offsets_host && out, "sdtw_plan_create: null pointer");
   SDTW_REQUIRE(nq >= 1, "sdtw_plan_create: nq=%d < 1", nq);
@@ -562,6 +817,27 @@ int sdtw_plan_create(const int64_t* offsets_host, int32_t nq, int dtype, sdtw_pl
   p->cus = cu_count();
   if (p->cus <= 0) p->cus = 256;
   choose_config(p);
+  p->rows = true;
+  while (p->nlong < nq && p->sorted_m[(size_t)p->nlong] > kRowsMaxM) ++p->nlong;
+  std::vector<std::pair<int32_t, int32_t>> reads;
+  for (int32_t i = p->nlong; i < nq; ++i)
+    reads.emplace_back(order[(size_t)i], p->sorted_m[(size_t)i]);
+  for (int i = 0; i < 2; ++i) {
+    p->lay[i] = new (std::nothrow) RowLayout(rows_layout(reads, i == 1, kRowsReads));
+    if (!p->lay[i]) {
+      delete p->lay[0];
+      delete p;
+      return set_error(SDTW_ENOMEM, "sdtw_plan_create: host allocation");
+    }
+    // the longest reference is cut into the most segments
+    for (int rounds : kRowsRounds) {
+      RowsArgs ra{};
+      ra.cus = p->cus;
+      int64_t w = 0;
+      (void)rows_cut(ra, *p->lay[i], INT32_MAX, rounds, RowCost{}, false, &w);
+      p->scratch_words = std::max(p->scratch_words, w);
+    }
+  }
   int rc = check_hip(hipMalloc((void**)&p->offs_dev, sizeof(int64_t) * (size_t)(nq + 1)),
                      "sdtw_plan_create: alloc");
   if (!rc) rc = check_hip(hipMalloc((void**)&p->order_dev, sizeof(int32_t) * (size_t)nq),
@@ -572,11 +848,18 @@ int sdtw_plan_create(const int64_t* offsets_host, int32_t nq, int dtype, sdtw_pl
                                     hipMemcpyHostToDevice), "sdtw_plan_create: copy");
   if (!rc) rc = check_hip(hipMemcpy(p->order_dev, order.data(), sizeof(int32_t) * (size_t)nq,
                                     hipMemcpyHostToDevice), "sdtw_plan_create: copy");
+  for (int i = 0; i < 2 && !rc && !reads.empty(); ++i) {
+    const size_t bytes = sizeof(RowPack) * p->lay[i]->packs.size();
+    rc = check_hip(hipMalloc((void**)&p->packs_dev[i], bytes), "sdtw_plan_create: alloc");
+    if (!rc)
+      rc = check_hip(hipMemcpy(p->packs_dev[i], p->lay[i]->packs.data(), bytes,
+                               hipMemcpyHostToDevice), "sdtw_plan_create: copy");
+  }
+  if (!rc && p->scratch_words)
+    rc = check_hip(hipMalloc((void**)&p->scratch, sizeof(uint64_t) * (size_t)p->scratch_words),
+                   "sdtw_plan_create: alloc");
   if (rc) {
-    (void)hipFree(p->offs_dev);
-    (void)hipFree(p->order_dev);
-    (void)hipFree(p->sched_dev);
-    delete p;
+    (void)plan_free(p);
     return rc;
   }
   *out = p;
@@ -627,6 +910,7 @@ int sdtw_plan_set_config(sdtw_plan plan, int strip, int chains, int bands, int w
   plan->bands = b2;
   plan->waves_per_cu = w2;
   if (band_rows >= 0) plan->band_rows = band_rows;
+  if (strip || chains || bands || waves_per_cu || band_rows >= 0) plan->rows = false;
   return SDTW_OK;
 }
 
@@ -643,13 +927,7 @@ int sdtw_plan_get_config(sdtw_plan plan, int* strip, int* chains, int* bands, in
 
 int sdtw_plan_destroy(sdtw_plan plan) {
   SDTW_REQUIRE(plan, "sdtw_plan_destroy: null plan");
-  hipError_t e1 = hipFree(plan->offs_dev);
-  hipError_t e2 = hipFree(plan->order_dev);
-  hipError_t e3 = hipFree(plan->sched_dev);
-  delete plan;
-  if (e1 != hipSuccess) return check_hip(e1, "sdtw_plan_destroy");
-  if (e2 != hipSuccess) return check_hip(e2, "sdtw_plan_destroy");
-  return check_hip(e3, "sdtw_plan_destroy");
+  return check_hip(plan_free(plan), "sdtw_plan_destroy");
 }
 
 // ---------------------------------------------------------------------------
@@ -712,6 +990,30 @@ static int align_batch_impl(sdtw_ref ref, sdtw_plan plan, const void* q_dev, voi
     }
     if (rc) return rc;
   }
+  if (plan->rows && plan->nlong < plan->nq) {
+    if (plan->cut_n != n) {
+      const bool f32 = plan->dtype == SDTW_F32;
+      RowsArgs ra{}, rb{};
+      ra.cus = rb.cus = plan->cus;
+      int64_t words = 0;
+      const double shared = rows_best_cut(ra, *plan->lay[0], false, n, f32, false,
+                                          plan->scratch_words, &words);
+      plan->cut_lay = rows_best_cut(rb, *plan->lay[1], true, n, f32, false, plan->scratch_words,
+                                    &words) < shared;
+      plan->cut = plan->cut_lay ? rb : ra;
+      plan->cut_n = n;
+    }
+    RowsArgs ra = plan->cut;
+    ra.ref = ref->data;
+    ra.n = n;
+    ra.q = q_dev;
+    ra.offs = plan->offs_dev;
+    ra.packs = plan->packs_dev[plan->cut_lay];
+    rows_scratch(ra, plan->scratch);
+    ra.cost = cost_dev;
+    ra.end = end_dev;
+    return check_hip(launch_align_rows(plan->dtype, ra, st, false), "sdtw_align_batch: launch");
+  }
   return SDTW_OK;
 }
 
@@ -737,6 +1039,70 @@ int sdtw_align_one(sdtw_ref ref, const void* q_dev, int32_t M, void* cost_dev, i
                    "sdtw_align_one: launch");
 }
 
+// One read of m <= kRowsMaxM rows, or a chunk of them that extends `row`,
+// spread over the device: the row-lane kernel with one read to a wave and,
+// behind it on long references, the row scan for references on which most
+// segments stay unsettled (without variation over thousands of columns), where
+// a single wave would walk them: 0.3 s instead of 2 ms for 250 rows x 10 M
+// equal values.  The scan's kernels end at once otherwise (about 8 us), so
+// shorter references, which one wave walks in milliseconds, go without.
+struct OneRead {
+  bool fits = false;  // the scratch allows it
+  RowsArgs rows{};
+  int cols = 0;       // of the row scan, 0: none
+  int64_t words = 0;  // scratch of the row-lane kernel (the row scan's follows)
+};
+constexpr int64_t kScanBehind = int64_t(1) << 20;  // columns
+constexpr int32_t kMostUnsettled = 16;             // segments left to their neighbours
+
+static int64_t one_words(const OneRead& o, int64_t n, int32_t m) {
+  return o.words + (o.cols ? wide_scratch_words(n, m, o.cols) : 0) + 1;
+}
+static OneRead one_read(sdtw_ref ref, const void* q, int32_t m, bool stream, int64_t max_words,
+                        void* cost, int32_t* end) {
+  OneRead o;
+  RowsArgs& a = o.rows;
+  a.ref = ref->data;
+  a.n = ref->n;
+  a.q = q;
+  a.cus = std::max(cu_count(), 1);
+  a.single_m = m;
+  const RowLayout lay = rows_layout({{0, m}}, true, 1);
+  a.pack = lay.packs[0];
+  if (ref->n >= kScanBehind) {
+    o.cols = wide_pick_cols(ref->n, ref->device);
+    max_words -= wide_scratch_words(ref->n, m, o.cols) + 1;
+  }
+  o.fits = rows_best_cut(a, lay, true, ref->n, false, stream, max_words, &o.words) >= 0.0;
+  if (!a.nhalo) o.cols = 0;
+  a.cost = cost;
+  a.end = end;
+  a.row_min_at = ref->n_pad - 1;
+  return o;
+}
+static hipError_t launch_one(sdtw_ref ref, OneRead& o, uint64_t* scratch, hipStream_t st,
+                             uint32_t* row = nullptr, int32_t rows_in = 0) {
+  RowsArgs& a = o.rows;
+  rows_scratch(a, scratch);
+  a.item.acc = row;
+  a.item.m = a.single_m;
+  a.item.m_old = rows_in;
+  const bool stream = row != nullptr;
+  if (!o.cols) return launch_align_rows(SDTW_I16, a, st, stream);
+  uint64_t* const scan = scratch + o.words;
+  uint32_t* const gate = (uint32_t*)(scan + wide_scratch_words(ref->n, a.single_m, o.cols));
+  a.skip = gate;
+  hipError_t e = launch_align_rows(SDTW_I16, a, st, stream, kRowsHalo);
+  if (e == hipSuccess)
+    e = launch_wide_gate(a.fail, a.nwaves, kMostUnsettled, gate, ref->n, a.single_m, o.cols, scan,
+                         st, rows_in > 0 ? row : nullptr);
+  if (e == hipSuccess) e = launch_align_rows(SDTW_I16, a, st, stream, kRowsSweep);
+  if (e == hipSuccess)
+    e = launch_align_wide(ref->data, ref->n, (const int16_t*)a.q, a.single_m, o.cols, scan,
+                          (int32_t*)a.cost, a.end, st, row, rows_in > 0, a.row_min_at, gate);
+  return e;
+}
+
 int sdtw_align_one_wide(sdtw_ref ref, const void* q_dev, int32_t M, int cols, void* cost_dev,
                         int32_t* end_dev, void* stream) {
   SDTW_REQUIRE(ref, "sdtw_align_one_wide: null reference");
@@ -747,6 +1113,7 @@ int sdtw_align_one_wide(sdtw_ref ref, const void* q_dev, int32_t M, int cols, vo
   SDTW_REQUIRE(cols == 0 || cols == 8 || cols == 16 || cols == 32 || cols == 64,
                "sdtw_align_one_wide: cols=%d not in {0, 8, 16, 32, 64}", cols);
   if (int rc = require_device(ref->device, "sdtw_align_one_wide")) return rc;
+  const bool rows = cols == 0 && M <= kRowsMaxM;
   if (cols == 0) cols = wide_pick_cols(ref->n, ref->device);
   SDTW_REQUIRE(wide_tiles(ref->n, cols) <= (int64_t)INT32_MAX,
                "sdtw_align_one_wide: reference too long for %d columns per thread", cols);
@@ -757,15 +1124,21 @@ int sdtw_align_one_wide(sdtw_ref ref, const void* q_dev, int32_t M, int cols, vo
   int rc = acquire_slot(ring, 1, &pick, "sdtw_align_one_wide");
   if (rc) return rc;
   DescSlot& sl = *pick;
-  rc = ensure_part(sl, wide_scratch_words(ref->n, M, cols));
+  OneRead one;
+  if (rows) one = one_read(ref, q_dev, M, false, INT64_MAX, cost_dev, end_dev);
+  rc = ensure_part(sl, rows ? one_words(one, ref->n, M) : wide_scratch_words(ref->n, M, cols));
   if (rc) return rc;
   auto tok = std::make_shared<CallToken>();
   tok->ev = event_get();
   if (!tok->ev) return set_error(SDTW_EDEVICE, "sdtw_align_one_wide: event creation failed");
   hipStream_t st = (hipStream_t)stream;
-  rc = check_hip(launch_align_wide(ref->data, ref->n, (const int16_t*)q_dev, M, cols, sl.part,
-                                   (int32_t*)cost_dev, end_dev, st),
-                 "sdtw_align_one_wide: launch");
+  if (rows) {
+    rc = check_hip(launch_one(ref, one, sl.part, st), "sdtw_align_one_wide: launch");
+  } else {
+    rc = check_hip(launch_align_wide(ref->data, ref->n, (const int16_t*)q_dev, M, cols, sl.part,
+                                     (int32_t*)cost_dev, end_dev, st),
+                   "sdtw_align_one_wide: launch");
+  }
   const int rc_ev = check_hip(hipEventRecord(tok->ev, st), "sdtw_align_one_wide: record");
   if (!rc_ev) sl.last = tok;
   return rc ? rc : rc_ev;
@@ -781,6 +1154,7 @@ int sdtw_align_one_wide_noalloc(sdtw_ref ref, const void* q_dev, int32_t M, int 
   SDTW_REQUIRE(cols == 0 || cols == 8 || cols == 16 || cols == 32 || cols == 64,
                "sdtw_align_one_wide_noalloc: cols=%d not in {0, 8, 16, 32, 64}", cols);
   if (int rc = require_device(ref->device, "sdtw_align_one_wide_noalloc")) return rc;
+  const bool rows = cols == 0 && M <= kRowsMaxM;
   if (cols == 0) cols = wide_pick_cols(ref->n, ref->device);
   SDTW_REQUIRE(wide_tiles(ref->n, cols) <= (int64_t)INT32_MAX,
                "sdtw_align_one_wide_noalloc: reference too long for %d columns per thread", cols);
@@ -793,6 +1167,12 @@ int sdtw_align_one_wide_noalloc(sdtw_ref ref, const void* q_dev, int32_t M, int 
   int rc = check_hip(wide_noalloc_scratch(ref->device, &scratch),
                      "sdtw_align_one_wide_noalloc: scratch address");
   if (rc) return rc;
+  if (rows) {
+    OneRead one = one_read(ref, q_dev, M, false, wide_noalloc_words(), cost_dev, end_dev);
+    if (one.fits)
+      return check_hip(launch_one(ref, one, scratch, (hipStream_t)stream),
+                       "sdtw_align_one_wide_noalloc: launch");
+  }
   return check_hip(launch_align_wide(ref->data, ref->n, (const int16_t*)q_dev, M, cols, scratch,
                                      (int32_t*)cost_dev, end_dev, (hipStream_t)stream),
                    "sdtw_align_one_wide_noalloc: launch");
@@ -824,6 +1204,7 @@ struct TuneVal {
   int strip, chains, bands, waves_per_cu;
   int32_t band_rows;
 };
+
 std::mutex g_tune_mu;
 std::map<TuneKey, TuneVal> g_tuned;  // best configuration per key
 bool g_tune_file_read = false;
@@ -914,11 +1295,15 @@ int sdtw_plan_autotune(sdtw_ref ref, sdtw_plan plan, const void* q_dev, void* co
   // LDS allows and at half that
   // and, with 3 or 4 bands, targets of a half and a third of the median read
   // (equal band heights for reads of different lengths)
+  // (the row-lane kernel takes reads of up to kRowsMaxM rows and has no shape to
+  // tune: without longer reads there is nothing to time)
+  plan->rows = true;
   std::vector<TuneVal> cand;
   const int32_t median_m = plan->sorted_m[plan->sorted_m.size() / 2];
   for (int strip : {16, 32})
     for (int chains : {1, 2})
       for (int bands : {1, 2, 3, 4}) {
+        if (plan->nlong == 0) continue;
         if (!valid_skew_config(strip, chains, bands)) continue;
         if (bands > 1 && plan->max_m < bands * skew_min_m(chains)) continue;
         std::vector<int32_t> targets = {0};
@@ -1006,6 +1391,7 @@ int sdtw_plan_use_tuned(sdtw_ref ref, sdtw_plan plan, int* found) {
     plan->bands = it->second.bands;
     plan->waves_per_cu = it->second.waves_per_cu;
     plan->band_rows = it->second.band_rows;
+    plan->rows = true;
   }
   return SDTW_OK;
 }
@@ -1201,14 +1587,21 @@ int sdtw_stream_extend(const sdtw_stream* streams, int32_t ns, const void* chunk
   int kStrip = ref->stream_strip.load();
   if (kStrip == 0) kStrip = g_stream_strip.load();
   if (kStrip == 0) kStrip = ref->n >= (int64_t(1) << 20) ? 32 : 16;
+  // The row-lane kernel takes chunks of up to kRowsMaxM rows, unless a launch
+  // shape was set; order[nskew ..) are its chunks.
+  const bool shaped = ref->stream_bands.load() || g_stream_bands.load() ||
+                      ref->stream_strip.load() || g_stream_strip.load();
+  int32_t nskew = ns;
+  if (!shaped)
+    for (nskew = 0; nskew < ns && len(order[(size_t)nskew]) > kRowsMaxM;) ++nskew;
   int32_t nbig = 0, max_band = 0;
-  while (nbig < ns && len(order[(size_t)nbig]) >= skew_min_m(kChains)) {
+  while (nbig < nskew && len(order[(size_t)nbig]) >= skew_min_m(kChains)) {
     max_band = std::max(max_band, skew_band_rows((int32_t)len(order[(size_t)nbig]), kChains, bands));
     ++nbig;
   }
   const size_t lds_max = (size_t)max_lds_bytes();
-  SDTW_REQUIRE(skew_lds_bytes(kStrip, kChains, bands, max_band, true) <= lds_max &&
-                   plain_lds_bytes(dtype, kStrip, max_m) <= lds_max,
+  SDTW_REQUIRE(nskew == 0 || (skew_lds_bytes(kStrip, kChains, bands, max_band, true) <= lds_max &&
+                              plain_lds_bytes(dtype, kStrip, max_m) <= lds_max),
                "sdtw_stream_extend: chunk of %d rows needs more LDS than available", max_m);
 
   const int dev = ref->device;
@@ -1228,20 +1621,55 @@ int sdtw_stream_extend(const sdtw_stream* streams, int32_t ns, const void* chunk
     it.out = i;
     it.pad = 0;
   }
+  RowsArgs ra{};
+  size_t npacks = 0;
+  if (nskew < ns) {
+    std::vector<std::pair<int32_t, int32_t>> chunks;
+    for (int32_t t = nskew; t < ns; ++t)
+      chunks.emplace_back(t, (int32_t)len(order[(size_t)t]));
+    ra.cus = cus;
+    RowsArgs rb = ra;
+    RowLayout lay = rows_layout(chunks, false, kRowsStreamReads);
+    RowLayout lay1 = rows_layout(chunks, true, kRowsStreamReads);
+    int64_t words = 0, words1 = 0;
+    const double shared = rows_best_cut(ra, lay, false, ref->n, dtype == SDTW_F32, true, INT64_MAX,
+                                        &words);
+    if (rows_best_cut(rb, lay1, true, ref->n, dtype == SDTW_F32, true, INT64_MAX, &words1) < shared) {
+      lay = std::move(lay1);
+      ra = rb;
+      words = words1;
+    }
+    npacks = lay.packs.size();
+    rc = ensure_part(sl, std::max<int64_t>(1, words));
+    if (rc) return rc;
+    rows_scratch(ra, sl.part);
+    std::copy(lay.packs.begin(), lay.packs.end(), sl.host_packs());
+    ra.ref = ref->data;
+    ra.n = ref->n;
+    ra.q = chunk_dev;
+    ra.items = sl.dev;
+    ra.packs = sl.dev_packs();
+    ra.cost = cost_dev;
+    ra.end = end_dev;
+    ra.row_min_at = ref->n_pad - 1;
+  }
   auto tok = std::make_shared<CallToken>();
   tok->ev = event_get();
   if (!tok->ev) return set_error(SDTW_EDEVICE, "sdtw_stream_extend: event creation failed");
   hipStream_t st = (hipStream_t)stream;
-  rc = check_hip(hipMemcpyAsync(sl.dev, sl.host, sizeof(StreamItem) * (size_t)ns,
-                                hipMemcpyHostToDevice, st),
+  // the items and, behind the slot's capacity of them, the packs
+  const size_t desc = npacks ? sizeof(StreamItem) * (size_t)sl.cap + sizeof(RowPack) * npacks
+                             : sizeof(StreamItem) * (size_t)ns;
+  rc = check_hip(hipMemcpyAsync(sl.dev, sl.host, desc, hipMemcpyHostToDevice, st),
                  "sdtw_stream_extend: descriptors");
   AlignArgs a{};
   a.ref = ref->data;
   a.n = ref->n;
   a.q = chunk_dev;
-  a.counter = (int32_t*)(sl.dev + sl.cap);
+  a.counter = sl.counter();
   a.cost = cost_dev;
   a.end = end_dev;
+  a.row_min_at = ref->n_pad - 1;
   int long_blocks = 0;
   if (!rc && nbig) {
     a.items = sl.dev;
@@ -1283,12 +1711,14 @@ int sdtw_stream_extend(const sdtw_stream* streams, int32_t ns, const void* chunk
                    "sdtw_stream_extend: launch");
     if (kStrip == 32) long_blocks = blocks;
   }
-  if (!rc && nbig < ns) {
+  if (!rc && nbig < nskew) {
     a.items = sl.dev + nbig;
-    a.nwork = ns - nbig;
+    a.nwork = nskew - nbig;
     a.max_m = (int32_t)len(order[(size_t)nbig]);
     rc = check_hip(launch_align_plain(dtype, kStrip, a, st, true), "sdtw_stream_extend: launch");
   }
+  if (!rc && npacks)
+    rc = check_hip(launch_align_rows(dtype, ra, st, true), "sdtw_stream_extend: launch");
   // the slot is busy until this point of the stream, whatever was enqueued
   const int rc_ev = check_hip(hipEventRecord(tok->ev, st), "sdtw_stream_extend: record");
   if (!rc_ev) sl.last = tok;
@@ -1313,6 +1743,7 @@ int sdtw_stream_extend_wide(sdtw_stream s, const void* chunk_dev, int32_t M, int
   SDTW_REQUIRE(cols == 0 || cols == 8 || cols == 16 || cols == 32 || cols == 64,
                "sdtw_stream_extend_wide: cols=%d not in {0, 8, 16, 32, 64}", cols);
   if (int rc = require_device(ref->device, "sdtw_stream_extend_wide")) return rc;
+  const bool rows = cols == 0 && M <= kRowsMaxM;
   if (cols == 0) cols = wide_pick_cols(ref->n, ref->device);
   SDTW_REQUIRE(wide_tiles(ref->n, cols) <= (int64_t)INT32_MAX,
                "sdtw_stream_extend_wide: reference too long for %d columns per thread", cols);
@@ -1323,15 +1754,23 @@ int sdtw_stream_extend_wide(sdtw_stream s, const void* chunk_dev, int32_t M, int
   int rc = acquire_slot(ring, 1, &pick, "sdtw_stream_extend_wide");
   if (rc) return rc;
   DescSlot& sl = *pick;
-  rc = ensure_part(sl, wide_scratch_words(ref->n, M, cols));
+  OneRead one;
+  if (rows) one = one_read(ref, chunk_dev, M, true, INT64_MAX, cost_dev, end_dev);
+  rc = ensure_part(sl, rows ? one_words(one, ref->n, M) : wide_scratch_words(ref->n, M, cols));
   if (rc) return rc;
   auto tok = std::make_shared<CallToken>();
   tok->ev = event_get();
   if (!tok->ev) return set_error(SDTW_EDEVICE, "sdtw_stream_extend_wide: event creation failed");
   hipStream_t st = (hipStream_t)stream;
-  rc = check_hip(launch_align_wide(ref->data, ref->n, (const int16_t*)chunk_dev, M, cols, sl.part,
-                                   (int32_t*)cost_dev, end_dev, st, s->row, s->rows > 0),
-                 "sdtw_stream_extend_wide: launch");
+  if (rows) {
+    rc = check_hip(launch_one(ref, one, sl.part, st, s->row, s->rows),
+                   "sdtw_stream_extend_wide: launch");
+  } else {
+    rc = check_hip(launch_align_wide(ref->data, ref->n, (const int16_t*)chunk_dev, M, cols,
+                                     sl.part, (int32_t*)cost_dev, end_dev, st, s->row,
+                                     s->rows > 0, ref->n_pad - 1),
+                   "sdtw_stream_extend_wide: launch");
+  }
   const int rc_ev = check_hip(hipEventRecord(tok->ev, st), "sdtw_stream_extend_wide: record");
   if (!rc_ev) sl.last = tok;
   if (!rc) rc = rc_ev;

@@ -135,6 +135,8 @@ struct AlignArgs {
   int32_t* end;          // int32[nq]
   int32_t single_m;      // used when offs == nullptr: one read of this length
   const StreamItem* items;  // streaming launches: work item descriptors
+  int64_t row_min_at;       // streaming launches: index of the word behind a resident row that
+                            // holds the row's minimum (cost encoding)
 };
 // Pull and placement state of a batch launch of the continuous-skew kernel:
 // a 64-bit pull word (items taken from the front of the work list in the low
@@ -156,6 +158,94 @@ hipError_t launch_align_skew(int dtype, int strip, int chains, int bands, int bl
 hipError_t launch_align_plain(int dtype, int strip, const AlignArgs& a, hipStream_t st,
                               bool stream = false);
 size_t plain_lds_bytes(int dtype, int strip, int max_m);
+
+// ---- launchers (rows_*.hip; the kernels are in rows.h) -----------------------
+// Row-lane kernel: reads of up to kRowsMaxM rows on the lanes of a wave, the
+// reference cut into column segments.
+constexpr int kRowsMaxM = 64 * 32;   // most rows per lane: 32
+constexpr int kRowsReads = 4;        // most reads that share a wave
+constexpr int kRowsStreamReads = 3;  // the same when resident rows are extended
+constexpr int kRowsPerLane[] = {2, 4, 6, 8, 10, 12, 14, 16, 20, 24, 28, 32};
+constexpr int kRowsClasses = 12;
+// The reads of one wave: read j owns lanes [lane0[j], lane0[j + 1]), each of
+// its pack's rows per lane or one fewer.
+struct RowPack {
+  int32_t nreads;
+  int32_t max_lanes;              // most lanes of a read
+  int32_t max_m;                  // longest of the reads
+  int32_t item[kRowsReads];       // read of the batch, or entry of the stream items
+  int32_t lane0[kRowsReads + 1];
+};
+// Packs of the same rows per lane, and the column segments each of them is
+// cut into (segcols columns, a multiple of 4, all but the last).  Waves are
+// numbered class by class, pack by pack, segment by segment.
+struct RowClass {
+  int32_t rows_per_lane;
+  int32_t first_pack, npacks;
+  int32_t nseg, segcols;
+  int32_t first_wave;             // of the sweep
+  int32_t first_halo;             // workgroup of the halo kernel (nseg - 1 per pack)
+  int32_t max_m, max_lanes;
+  int64_t bound_at;               // first word of the columns left of its segments
+  int64_t result_at;              // first of its results (see kRowsGroup)
+};
+// A read's results of `nseg` segments meet in groups of kRowsGroup segments
+// and then in one: rows_groups(nseg) groups and the whole, each a smallest
+// (cost, column) and a count of segments done.  (Every wave of a read on one
+// word costs about 20 ns each: 40 us for 2,000 segments.)
+constexpr int kRowsGroup = 32;
+__host__ __device__ constexpr int32_t rows_groups(int32_t nseg) {
+  return nseg > kRowsGroup ? (nseg + kRowsGroup - 1) / kRowsGroup : 0;
+}
+// Lanes a read of m rows takes at R rows per lane, or 0 if it does not fit: L
+// lanes hold between L (R - 1) and L R rows.
+inline int32_t rows_lanes(int32_t m, int R) {
+  const int32_t lanes = (m + R - 1) / R;
+  return lanes <= kLanes && m >= lanes * (R - 1) ? lanes : 0;
+}
+__host__ __device__ constexpr int64_t rows_bound_words(int R) {  // a column of a pack
+  return int64_t(kLanes) * (R + 1);
+}
+
+struct RowsArgs {
+  const uint32_t* ref;      // padded device layout
+  int64_t n;                // true reference length
+  const void* q;            // query values
+  const int64_t* offs;      // batch: CSR offsets (null: one read of single_m values)
+  const StreamItem* items;  // stream: work items (null: the one in `item`)
+  const RowPack* packs;     // device (null: the one in `pack`)
+  int32_t single_m;
+  int32_t cus;              // compute units of the device
+  int32_t dpp;              // one read per pack, rows handed on in registers
+  int32_t nclasses;
+  int32_t nwaves, nhalo;    // waves of the sweep, workgroups of the halo kernel
+  int64_t nresults;         // result words
+  uint32_t* bound;          // columns left of the segments
+  uint64_t* keys;           // per result, the smallest (cost, column) so far
+  uint32_t* done;           // per result, segments (or groups) finished
+  uint32_t* fail;           // per wave of the sweep, 1 if its left column is unknown
+  const uint32_t* skip;     // one read: the sweep does nothing if this word is set (may be null)
+  void* cost;
+  int32_t* end;
+  int64_t row_min_at;       // stream: index of the word behind a resident row that holds its
+                            // minimum
+  RowPack pack;
+  StreamItem item;
+  RowClass cls[kRowsClasses];
+};
+// Enqueues the halo kernel (if there are segments), then the sweep, or one of
+// the two.
+enum RowsPart { kRowsBoth = 3, kRowsHalo = 1, kRowsSweep = 2 };
+hipError_t launch_rows_i16(const RowsArgs& a, hipStream_t st, int parts);
+hipError_t launch_rows_f32(const RowsArgs& a, hipStream_t st, int parts);
+hipError_t launch_rows_i16_stream(const RowsArgs& a, hipStream_t st, int parts);
+hipError_t launch_rows_f32_stream(const RowsArgs& a, hipStream_t st, int parts);
+inline hipError_t launch_align_rows(int dtype, const RowsArgs& a, hipStream_t st, bool stream,
+                                    int parts = kRowsBoth) {
+  if (dtype == SDTW_I16)
+    return stream ? launch_rows_i16_stream(a, st, parts) : launch_rows_i16(a, st, parts);
+  return stream ? launch_rows_f32_stream(a, st, parts) : launch_rows_f32(a, st, parts);
+}
 
 // ---- launchers (scores.hip) -------------------------------------------------
 // Best and runner-up ends of the resident rows items[i].acc (n columns), out
@@ -194,7 +284,7 @@ hipError_t launch_events_continue(const float* raw, const int64_t* ranges, const
 // (cleared by it, in order on `st`).  `row` (n values, optional): the last
 // row is written there; with `row_in` the rows extend it (it holds the row
 // before the first of the m rows, at most 4,096 rows in all) instead of
-// starting from the free-start zeros.
+// starting from the free-start zeros; its minimum goes to row[row_min_at].
 int64_t wide_tiles(int64_t n, int cols);
 int64_t wide_scratch_words(int64_t n, int32_t m, int cols);
 int wide_pick_cols(int64_t n, int device);  // columns per thread for sdtw_align_one_wide(cols=0)
@@ -205,6 +295,13 @@ int64_t wide_noalloc_words();
 hipError_t wide_noalloc_scratch(int device, uint64_t** out);
 hipError_t launch_align_wide(const uint32_t* ref, int64_t n, const int16_t* q, int32_t m,
                              int cols, uint64_t* scratch, int32_t* cost, int32_t* end,
-                             hipStream_t st, uint32_t* row = nullptr, bool row_in = false);
+                             hipStream_t st, uint32_t* row = nullptr, bool row_in = false,
+                             int64_t row_min_at = 0, uint32_t* gate = nullptr);
+// Sets *gate if more than `limit` of the flags are set, and clears the scratch
+// then: launch_align_wide with that gate, later on the same stream, works only
+// if it is set.
+hipError_t launch_wide_gate(const uint32_t* flags, int32_t nflags, int32_t limit, uint32_t* gate,
+                            int64_t n, int32_t m, int cols, uint64_t* scratch, hipStream_t st,
+                            const uint32_t* row);
 
 }  // namespace sdtw

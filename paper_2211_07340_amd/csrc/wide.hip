@@ -276,6 +276,9 @@ __device__ uint32_t look_back(int32_t tile, int32_t ntiles, int32_t i, int32_t m
   }
 }
 
+// A gated launch (see launch_wide_gate) has nothing to do unless its gate is set.
+__device__ __forceinline__ bool shut(const uint32_t* gate) { return gate && *gate == 0u; }
+
 // ROW: a resident row to extend (row_in) or to write (compiled apart, so
 // that the single-query form keeps its registers and so its tiles per CU).
 template <int C, bool LowReg, bool ROW>
@@ -283,7 +286,8 @@ __global__ __launch_bounds__(kWideThreads, LowReg ? 3 : 1) void k_align_wide(
     const uint32_t* __restrict__ ref, int64_t n, int32_t ntiles, const int16_t* __restrict__ q,
     int32_t m, uint64_t* __restrict__ flags, uint64_t* __restrict__ tile_key,
     uint32_t* __restrict__ ctrl, uint32_t* __restrict__ row, int row_in,
-    const uint64_t* __restrict__ left_of_tile) {
+    const uint64_t* __restrict__ left_of_tile, const uint32_t* __restrict__ gate) {
+  if (shut(gate)) return;
   constexpr int T = kWideThreads * C;
   __shared__ uint32_t sa[kWideThreads / 64], sd[kWideThreads / 64];
   __shared__ uint32_t lastcol[2][kWideThreads];
@@ -412,19 +416,48 @@ __global__ __launch_bounds__(kWideThreads, LowReg ? 3 : 1) void k_align_wide(
 // Flags and the ticket cleared for the next launch (a kernel, not a memset,
 // so that the call can be captured in a graph); when a resident row is
 // extended, the old value left of every tile (T columns each) copied aside.
-__global__ void k_wide_clear(uint64_t* __restrict__ flags, int64_t nflags,
-                             uint32_t* __restrict__ ctrl, const uint32_t* __restrict__ row,
-                             int64_t T, int32_t ntiles, uint64_t* __restrict__ left_of_tile) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < nflags) flags[i] = 0;
-  if (i < 2) ctrl[i] = 0;
-  if (row && i < ntiles) left_of_tile[i] = i > 0 ? row[i * T - 1] : 0u;
+struct WideClear {
+  uint64_t* flags;
+  int64_t nflags;
+  uint32_t* ctrl;
+  const uint32_t* row;
+  int64_t T;
+  int32_t ntiles;
+  uint64_t* left_of_tile;
+  __device__ __forceinline__ void at(int64_t i) const {
+    if (i < nflags) flags[i] = 0;
+    if (i < 2) ctrl[i] = 0;
+    if (row && i < ntiles) left_of_tile[i] = i > 0 ? row[i * T - 1] : 0u;
+  }
+};
+__global__ void k_wide_clear(WideClear c) { c.at((int64_t)blockIdx.x * blockDim.x + threadIdx.x); }
+
+// The same by one workgroup, if more than `limit` of the n flags are set (few
+// calls come to that; the others read the flags and end).
+__global__ __launch_bounds__(1024) void k_wide_gate(const uint32_t* __restrict__ set, int32_t n,
+                                                    int32_t limit, uint32_t* __restrict__ gate,
+                                                    WideClear c) {
+  __shared__ int32_t part[16];
+  int32_t mine = 0;
+  for (int32_t i = (int32_t)threadIdx.x; i < n; i += 1024) mine += (int32_t)set[i];
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) mine += __shfl_xor(mine, off);
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = mine;
+  __syncthreads();
+  int32_t all = 0;
+  for (int w = 0; w < 16; ++w) all += part[w];
+  if (threadIdx.x == 0) *gate = all > limit ? 1u : 0u;
+  if (all <= limit) return;
+  for (int64_t i = (int64_t)threadIdx.x; i < c.nflags; i += 1024) c.at(i);
 }
 
 __global__ __launch_bounds__(kWideThreads) void k_wide_final(const uint64_t* __restrict__ tile_key,
                                                              int32_t ntiles,
                                                              const uint32_t* __restrict__ ctrl,
-                                                             int32_t* cost, int32_t* end) {
+                                                             int32_t* cost, int32_t* end,
+                                                             uint32_t* row_min,
+                                                             const uint32_t* __restrict__ gate) {
+  if (shut(gate)) return;
   __shared__ uint64_t sk[kWideThreads / 64];
   uint64_t k = ~0ull;
   for (int32_t t = threadIdx.x; t < ntiles; t += kWideThreads) k = tile_key[t] < k ? tile_key[t] : k;
@@ -443,6 +476,7 @@ __global__ __launch_bounds__(kWideThreads) void k_wide_final(const uint64_t* __r
     const bool aborted = ctrl[1] != 0;
     *cost = aborted ? -1 : (int32_t)(uint32_t)(k >> 32);
     *end = aborted ? -1 : (int32_t)(uint32_t)k;
+    if (row_min) *row_min = (uint32_t)(k >> 32);
   }
 }
 
@@ -456,26 +490,35 @@ int resident_tiles(const void* fn) {
   return per_cu * cus;
 }
 
+// What a launch clears, and where it lies in the scratch (nflags >= 2 ntiles:
+// clearing the flags' words one by one covers every tile).
+WideClear wide_clear(int64_t n, int32_t m, int cols, uint64_t* scratch, const uint32_t* row) {
+  WideClear c;
+  c.T = (int64_t)kWideThreads * cols;
+  c.ntiles = (int32_t)((n + c.T - 1) / c.T);
+  const int64_t ngroups = (c.ntiles + kLookback - 1) / kLookback;
+  c.nflags = 2 * (int64_t)m * c.ntiles + (int64_t)m * ngroups;
+  c.flags = scratch;
+  uint64_t* const tile_key = scratch + c.nflags;
+  c.ctrl = (uint32_t*)(tile_key + c.ntiles);
+  c.left_of_tile = tile_key + c.ntiles + 1;  // after the two control words
+  c.row = row;
+  return c;
+}
+
 template <int C, bool LowReg, bool ROW>
 hipError_t launch_c(const uint32_t* ref, int64_t n, const int16_t* q, int32_t m,
                     uint64_t* scratch, int32_t* cost, int32_t* end, hipStream_t st,
-                    uint32_t* row, bool row_in) {
-  const int64_t T = (int64_t)kWideThreads * C;
-  const int32_t ntiles = (int32_t)((n + T - 1) / T);
-  const int64_t ngroups = (ntiles + kLookback - 1) / kLookback;
-  const int64_t nflags = 2 * (int64_t)m * ntiles + (int64_t)m * ngroups;
-  uint64_t* flags = scratch;
-  uint64_t* tile_key = flags + nflags;
-  uint32_t* ctrl = (uint32_t*)(tile_key + ntiles);
-  uint64_t* left_of_tile = tile_key + ntiles + 1;  // after the two control words
-  // (nflags >= 2 * ntiles: the clearing grid covers every tile)
-  hipLaunchKernelGGL(k_wide_clear, dim3((unsigned)((nflags + 255) / 256)), dim3(256), 0, st,
-                     flags, nflags, ctrl, row_in ? row : nullptr, T, ntiles, left_of_tile);
-  hipLaunchKernelGGL((k_align_wide<C, LowReg, ROW>), dim3((unsigned)ntiles), dim3(kWideThreads), 0,
-                     st, ref, n, ntiles, q, m, flags, tile_key, ctrl, row, row_in ? 1 : 0,
-                     left_of_tile);
-  hipLaunchKernelGGL(k_wide_final, dim3(1), dim3(kWideThreads), 0, st, tile_key, ntiles, ctrl,
-                     cost, end);
+                    uint32_t* row, bool row_in, int64_t row_min_at, uint32_t* gate) {
+  const WideClear c = wide_clear(n, m, C, scratch, row_in ? row : nullptr);
+  uint64_t* const tile_key = c.flags + c.nflags;
+  if (!gate)
+    hipLaunchKernelGGL(k_wide_clear, dim3((unsigned)((c.nflags + 255) / 256)), dim3(256), 0, st, c);
+  hipLaunchKernelGGL((k_align_wide<C, LowReg, ROW>), dim3((unsigned)c.ntiles), dim3(kWideThreads),
+                     0, st, ref, n, c.ntiles, q, m, c.flags, tile_key, c.ctrl, row, row_in ? 1 : 0,
+                     c.left_of_tile, gate);
+  hipLaunchKernelGGL(k_wide_final, dim3(1), dim3(kWideThreads), 0, st, tile_key, c.ntiles, c.ctrl,
+                     cost, end, row ? row + row_min_at : nullptr, gate);
   return hipGetLastError();
 }
 
@@ -532,30 +575,39 @@ namespace {
 template <bool ROW>
 hipError_t launch_row(const uint32_t* ref, int64_t n, const int16_t* q, int32_t m, int cols,
                       uint64_t* scratch, int32_t* cost, int32_t* end, hipStream_t st,
-                      uint32_t* row, bool row_in) {
+                      uint32_t* row, bool row_in, int64_t row_min_at, uint32_t* gate) {
   switch (cols) {
-    case 8: return launch_c<8, false, ROW>(ref, n, q, m, scratch, cost, end, st, row, row_in);
-    case 16: return launch_c<16, false, ROW>(ref, n, q, m, scratch, cost, end, st, row, row_in);
+    case 8: return launch_c<8, false, ROW>(ref, n, q, m, scratch, cost, end, st, row, row_in, row_min_at, gate);
+    case 16: return launch_c<16, false, ROW>(ref, n, q, m, scratch, cost, end, st, row, row_in, row_min_at, gate);
     case 32: {
       // the low-register form when the plain one would run in more rounds
       if (wide_tiles(n, 32) > resident_tiles((const void*)k_align_wide<32, false, ROW>))
-        return launch_c<32, true, ROW>(ref, n, q, m, scratch, cost, end, st, row, row_in);
-      return launch_c<32, false, ROW>(ref, n, q, m, scratch, cost, end, st, row, row_in);
+        return launch_c<32, true, ROW>(ref, n, q, m, scratch, cost, end, st, row, row_in, row_min_at, gate);
+      return launch_c<32, false, ROW>(ref, n, q, m, scratch, cost, end, st, row, row_in, row_min_at, gate);
     }
-    case 64: return launch_c<64, false, ROW>(ref, n, q, m, scratch, cost, end, st, row, row_in);
+    case 64: return launch_c<64, false, ROW>(ref, n, q, m, scratch, cost, end, st, row, row_in, row_min_at, gate);
     default: return hipErrorInvalidValue;
   }
 }
 
 }  // namespace
 
+hipError_t launch_wide_gate(const uint32_t* flags, int32_t nflags, int32_t limit, uint32_t* gate,
+                            int64_t n, int32_t m, int cols, uint64_t* scratch, hipStream_t st,
+                            const uint32_t* row) {
+  hipLaunchKernelGGL(k_wide_gate, dim3(1), dim3(1024), 0, st, flags, nflags, limit, gate,
+                     wide_clear(n, m, cols, scratch, row));
+  return hipGetLastError();
+}
+
 hipError_t launch_align_wide(const uint32_t* ref, int64_t n, const int16_t* q, int32_t m,
                              int cols, uint64_t* scratch, int32_t* cost, int32_t* end,
-                             hipStream_t st, uint32_t* row, bool row_in) {
+                             hipStream_t st, uint32_t* row, bool row_in, int64_t row_min_at,
+                             uint32_t* gate) {
   if (n < 1 || m < 1 || wide_tiles(n, cols) > INT_MAX || (row_in && !row))
     return hipErrorInvalidValue;
-  return row ? launch_row<true>(ref, n, q, m, cols, scratch, cost, end, st, row, row_in)
-             : launch_row<false>(ref, n, q, m, cols, scratch, cost, end, st, row, row_in);
+  return row ? launch_row<true>(ref, n, q, m, cols, scratch, cost, end, st, row, row_in, row_min_at, gate)
+             : launch_row<false>(ref, n, q, m, cols, scratch, cost, end, st, row, row_in, row_min_at, gate);
 }
 
 }  // namespace sdtw
