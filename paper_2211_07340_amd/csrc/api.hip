@@ -519,7 +519,8 @@ int sdtw_prepare_reference(const uint8_t* genome_dev, int64_t L, const float* ta
   SDTW_REQUIRE(isfinite(scale) && scale > 0.0, "sdtw_prepare_reference: scale must be > 0");
   hipStream_t st = (hipStream_t)stream;
   double* scratch = nullptr;
-  int rc = check_hip(hipMallocAsync((void**)&scratch, kRefPartials * sizeof(double), st),
+  int rc = check_hip(hipMallocAsync((void**)&scratch,
+                                    ref_scratch_doubles(2 * (L - k + 1)) * sizeof(double), st),
                      "sdtw_prepare_reference: scratch");
   if (rc) return rc;
   rc = check_hip(launch_prepare_reference(genome_dev, L, table_dev, k, scale, z_dev, codes_dev,
