@@ -215,25 +215,32 @@ static RowLayout rows_layout(const std::vector<std::pair<int32_t, int32_t>>& rea
 }
 
 // The time of a launch in cycles, by a model of the sweep and the halo
-// kernel.  A SIMD issues one of a step's instructions (8 R for the cells, on
-// float32 counted as if it had two per cell, and a few more) per `cycles`,
-// by the waves on it: measured on the sweep at 16 rows per lane (4,096 reads
-// of 250 rows x 59,796 columns, 1,024 waves per round) and, alike, on bare
-// v_min3_u32 and v_sad_u32 (6.2, 5.05 and 4.55 with one, two and four
-// waves).  Rows handed on through LDS, a lone wave waits for the round trip
-// (about 420 cycles), and four LDS operations a step of 8 to 10 cycles for
-// each of the CU's four SIMDs bound the narrowest packs (240 cycles a step at
-// 4 rows per lane with three waves, 190 with four).
+// kernel: a wave's share of its SIMD for a step at R rows per lane, with
+// `waves` on the SIMD, is cells[] for each row and over[] besides (LDS, rows
+// handed on, latency that nothing hides).  Fitted to the sweep's times at 2 to
+// 32 rows per lane x 1, 2, 3, 4 and 8 waves (29,892 columns, both types and
+// both ways to hand rows on; within 7% from 4 rows per lane up).  The float32
+// cells do best with two or four waves: 16 rows per lane x 59,796 columns
+// reach 18.0 TCUPS with two, 16.0 with three and 17.4 with four, the int16
+// cells 15.7, 16.4 and 16.5.  Resident rows cost a step about 170, 110 and 90
+// cycles more (86 packs at 20 rows per lane x 59,796 columns).
 struct RowCost {
-  bool dpp, f32;
-  double step(int R, double rounds) const {  // of all of a SIMD's waves
-    static const double kI16[] = {6.2, 6.2, 5.05, 4.7, 4.5}, kF32[] = {6.0, 6.0, 4.4, 4.75, 4.25};
-    const double ops = 8.0 * R + (dpp ? 10.0 : 2.0);
-    const double cycles = (f32 ? kF32 : kI16)[(int)std::min(rounds, 4.0)];
-    const double wave = std::max(ops * cycles, dpp ? 0.0 : (rounds < 4.0 ? 240.0 : 190.0));
-    return std::max(rounds * wave, (dpp ? 0.0 : 420.0) + 6.2 * ops);
+  bool dpp, f32, stream;
+  double step(int R, double waves) const {
+    struct Fit { double over[4], cells[4]; };
+    static const Fit kLds[] = {{{230, 105, 80, 72}, {33.6, 35.2, 34.8, 34.8}},
+                               {{205, 115, 75, 92}, {51.5, 31.6, 36.6, 32.2}}};
+    static const Fit kDpp[] = {{{165, 95, 85, 85}, {33.6, 33.1, 32.5, 32.5}},
+                               {{150, 113, 82, 80}, {51.7, 39.2, 37.4, 36.2}}};
+    const Fit& f = (dpp ? kDpp : kLds)[f32];
+    const int w = (int)std::min(std::max(waves, 1.0), 4.0) - 1;
+    static const double kResident[4] = {170, 110, 90, 90};
+    return f.over[w] + f.cells[w] * R + (stream ? kResident[w] : 0.0);
   }
 };
+// What a step costs besides its cells, in rows: waves of different rows per
+// lane end together when columns are dealt out by rows and this.
+constexpr double kRowsStepOver = 2.2;
 
 // Most waves of a SIMD a launch is cut into, one after another or at once:
 // the bound of the scratch that its boundary columns need.
@@ -246,8 +253,8 @@ constexpr int kRowsRounds[] = {1, 2, 3, 4, 6, 8, 12, 16};
 static double rows_cut(RowsArgs& a, const RowLayout& lay, int64_t n, double rounds, RowCost cost,
                        bool stream, int64_t* words) {
   const int64_t room = (int64_t)(a.cus * 4 * rounds);
-  auto columns = [&](const RowClass& c, double tau) {  // a segment's, for waves of tau instructions
-    const double cols = 4.0 * tau / (8.0 * c.rows_per_lane + 2.0);
+  auto columns = [&](const RowClass& c, double tau) {  // a segment's, for waves of tau row steps
+    const double cols = 4.0 * (tau / (c.rows_per_lane + kRowsStepOver) - c.max_lanes);
     const int64_t least = std::max<int64_t>(64, c.max_m / 4);
     const int64_t whole = (n + 63) & ~(int64_t)63;
     return std::min(whole, (std::max(least, (int64_t)std::min(cols, 2e9)) + 63) & ~(int64_t)63);
@@ -261,7 +268,7 @@ static double rows_cut(RowsArgs& a, const RowLayout& lay, int64_t n, double roun
     return w;
   };
   // the shortest waves that the SIMDs have room for
-  double lo = 0.0, hi = 4.0 * (double)n * 300.0;
+  double lo = 0.0, hi = (0.25 * (double)n + 2 * kLanes) * (32.0 + kRowsStepOver);
   for (int i = 0; i < 40 && count(lo) > room && hi - lo > 4e-3 * hi; ++i) {
     const double mid = 0.5 * (lo + hi);
     (count(mid) > room ? lo : hi) = mid;
@@ -291,29 +298,36 @@ static double rows_cut(RowsArgs& a, const RowLayout& lay, int64_t n, double roun
   a.nresults = results;
   *words = a.nhalo ? results + (results + 1) / 2 + ((int64_t)a.nwaves + 1) / 2 + (bound + 1) / 2
                    : 0;
-  // The sweep: waves of one class are equally long, so SIMDs that hold fewer
-  // of them wait for the others; of several classes the shorter fill the gaps
-  // but the last.  A launch takes about 8 us besides its steps.
+  // The sweep: up to four waves of a SIMD run side by side and the fullest
+  // SIMD ends last; more follow one another, and what is left at the end is
+  // about how far the longest wave exceeds the mean, or the last round's gap.
+  // Each pack's last segment is shorter than the others, so many rounds of
+  // short waves fill the SIMDs better than one (1,024 reads of 250 to 500
+  // rows x 10 M columns: 248 ms with 4, 231 with 8, 224 with 16).  A launch
+  // takes about 8 us besides its steps.
   const double simds = 4.0 * a.cus, per = a.nwaves / simds;
   double work = 0.0, longest = 0.0, halo = 0.0;
   for (int k = 0; k < a.nclasses; ++k) {
     const RowClass& c = a.cls[k];
     const double steps = c.segcols / 4.0 + c.max_lanes;
-    const double wave = steps * cost.step(c.rows_per_lane, std::ceil(per)) / std::ceil(per);
+    const double wave = steps * cost.step(c.rows_per_lane, std::ceil(per));
     work += wave * (double)c.nseg * c.npacks / simds;
     longest = std::max(longest, wave);
     if (c.nseg > 1) {
       const double h = ((stream ? 1.33 : 1.125) * c.max_m + 64.0) / 4.0 + c.max_lanes;
-      const double rounds = 2.0 * a.nhalo / simds;
-      // (its steps are guarded one by one: measured 474 cycles at 8 rows per lane
-      // through LDS, 380 with register moves, 1.6 and 1.15 times a sweep's)
-      halo += h * (double)(c.nseg - 1) * c.npacks / a.nhalo * (cost.dpp ? 1.15 : 1.6) *
-              (rounds > 1.0 ? rounds / std::ceil(rounds) : 1.0) *
-              cost.step(c.rows_per_lane, std::ceil(rounds));
+      halo += h * (double)(c.nseg - 1) * c.npacks / a.nhalo *
+              (RowCost{cost.dpp, cost.f32, false}.step(c.rows_per_lane, 4.0) +
+               (cost.dpp ? 0.0 : 20.0));
     }
   }
-  const double sweep = per > 4.0 ? work + 0.5 * longest : std::max(work, longest * std::ceil(per));
-  return sweep + halo + (a.nhalo ? 40000.0 : 20000.0);
+  const double mean = work / per;
+  const double sweep = per > 4.0 ? work + std::max(longest - mean, 0.5 * (std::ceil(per) - per) * mean)
+                                 : std::max(work, longest * std::ceil(per));
+  // A halo is two waves, and the launch takes about one more (1.0 to 1.3 at 2
+  // to 30 rows per lane x 1 to 7 waves per SIMD): it ends with those that try
+  // again.
+  halo *= std::max(2.0 * a.nhalo / simds, 1.0) + (cost.dpp ? 1.0 : 1.3);
+  return sweep + halo + (a.nhalo ? 35000.0 : 20000.0);
 }
 
 // The best of the cuts with scratch of at most most_words words (its modelled
@@ -326,7 +340,7 @@ static double rows_best_cut(RowsArgs& a, const RowLayout& lay, bool alone, int64
   for (int dpp = 0; dpp <= (alone ? 1 : 0); ++dpp) {
     for (int rounds : kRowsRounds) {
       int64_t w = 0;
-      const double t = rows_cut(at, lay, n, rounds, RowCost{dpp != 0, f32}, stream, &w);
+      const double t = rows_cut(at, lay, n, rounds, RowCost{dpp != 0, f32, stream}, stream, &w);
       if (w > most_words && at.nhalo) continue;
       if (best < 0.0 || t < best) {
         best = t;

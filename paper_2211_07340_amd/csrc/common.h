@@ -165,8 +165,12 @@ size_t plain_lds_bytes(int dtype, int strip, int max_m);
 constexpr int kRowsMaxM = 64 * 32;   // most rows per lane: 32
 constexpr int kRowsReads = 4;        // most reads that share a wave
 constexpr int kRowsStreamReads = 3;  // the same when resident rows are extended
-constexpr int kRowsPerLane[] = {2, 4, 6, 8, 10, 12, 14, 16, 20, 24, 28, 32};
-constexpr int kRowsClasses = 12;
+// Every even number of rows: lanes fill to 94-95% over reads of 100 to 2,000 and
+// of 250 to 500 rows, 91-92% with steps of four from 16 up (8,192 reads x 59,796
+// columns: 33.6 to 32.4 ms; 1,024 x 10 M: 230.5 to 225.0 ms).
+constexpr int kRowsPerLane[] = {2,  4,  6,  8,  10, 12, 14, 16,
+                                18, 20, 22, 24, 26, 28, 30, 32};
+constexpr int kRowsClasses = 16;
 // The reads of one wave: read j owns lanes [lane0[j], lane0[j + 1]), each of
 // its pack's rows per lane or one fewer.
 struct RowPack {
@@ -207,30 +211,36 @@ __host__ __device__ constexpr int64_t rows_bound_words(int R) {  // a column of 
   return int64_t(kLanes) * (R + 1);
 }
 
-struct RowsArgs {
+// What the waves of every class share.  The kernels take a copy in registers:
+// read through the whole argument, from a sweep per class, the compiler gives
+// up on following it and copies all classes to scratch memory, in every lane
+// (1 KB: 162 registers spilled).
+struct RowsCall {
   const uint32_t* ref;      // padded device layout
   int64_t n;                // true reference length
   const void* q;            // query values
   const int64_t* offs;      // batch: CSR offsets (null: one read of single_m values)
   const StreamItem* items;  // stream: work items (null: the one in `item`)
-  const RowPack* packs;     // device (null: the one in `pack`)
   int32_t single_m;
+  uint32_t* bound;          // columns left of the segments
+  uint64_t* keys;           // per result, the smallest (cost, column) so far
+  uint32_t* done;           // per result, segments (or groups) finished
+  uint32_t* fail;           // per wave of the sweep, 1 if its left column is unknown
+  void* cost;
+  int32_t* end;
+  int64_t row_min_at;       // stream: index of the word behind a resident row that holds its
+                            // minimum
+  StreamItem item;
+};
+struct RowsArgs : RowsCall {
+  const RowPack* packs;     // device (null: the one in `pack`)
   int32_t cus;              // compute units of the device
   int32_t dpp;              // one read per pack, rows handed on in registers
   int32_t nclasses;
   int32_t nwaves, nhalo;    // waves of the sweep, workgroups of the halo kernel
   int64_t nresults;         // result words
-  uint32_t* bound;          // columns left of the segments
-  uint64_t* keys;           // per result, the smallest (cost, column) so far
-  uint32_t* done;           // per result, segments (or groups) finished
-  uint32_t* fail;           // per wave of the sweep, 1 if its left column is unknown
   const uint32_t* skip;     // one read: the sweep does nothing if this word is set (may be null)
-  void* cost;
-  int32_t* end;
-  int64_t row_min_at;       // stream: index of the word behind a resident row that holds its
-                            // minimum
   RowPack pack;
-  StreamItem item;
   RowClass cls[kRowsClasses];
 };
 // Enqueues the halo kernel (if there are segments), then the sweep, or one of

@@ -131,7 +131,7 @@ __device__ __forceinline__ void cells4(const uint32_t (&x)[R], uint32_t (&h)[R],
 __device__ __forceinline__ RowPack get_pack(const RowsArgs& a, int32_t i) {
   return a.packs ? a.packs[i] : a.pack;
 }
-__device__ __forceinline__ StreamItem get_item(const RowsArgs& a, int32_t i) {
+__device__ __forceinline__ StreamItem get_item(const RowsCall& a, int32_t i) {
   return a.items ? a.items[i] : a.item;
 }
 
@@ -148,7 +148,7 @@ struct LaneRows {
 };
 
 template <int R, bool STREAM>
-__device__ __forceinline__ LaneRows lane_rows(const RowsArgs& a, const RowPack& pk, int lane) {
+__device__ __forceinline__ LaneRows lane_rows(const RowsCall& a, const RowPack& pk, int lane) {
   LaneRows w{};
   int32_t lane0 = 0, lane1 = pk.lane0[1];
   w.item = pk.item[0];
@@ -185,7 +185,7 @@ __device__ __forceinline__ LaneRows lane_rows(const RowsArgs& a, const RowPack& 
 }
 
 template <class F, int R>
-__device__ __forceinline__ void load_rows(const RowsArgs& a, const LaneRows& w,
+__device__ __forceinline__ void load_rows(const RowsCall& a, const LaneRows& w,
                                           uint32_t (&x)[R]) {
   const typename F::qin* q = (const typename F::qin*)a.q;
 #pragma unroll
@@ -200,7 +200,7 @@ __device__ __forceinline__ void load_rows(const RowsArgs& a, const LaneRows& w,
 // instead of through LDS, which costs eight instructions a step more and
 // saves the LDS round trip, the better bargain where a SIMD has one wave.
 template <class F, int R, bool STREAM, bool DPP, bool MAIN>
-__device__ __forceinline__ void sweep(const RowsArgs& a, const RowPack& pk, const LaneRows& w,
+__device__ __forceinline__ void sweep(const RowsCall& a, const RowPack& pk, const LaneRows& w,
                                       char* lds, int32_t c0, int32_t ngroups, int32_t c1,
                                       const uint32_t (&x)[R], uint32_t (&h)[R], uint32_t& sd,
                                       uint32_t (&best)[Lds<STREAM>::kPairs],
@@ -341,7 +341,8 @@ __device__ __forceinline__ void sweep(const RowsArgs& a, const RowPack& pk, cons
       const int32_t lead = pk.max_lanes - 1 - s0;  // steps until every lane has started
       int32_t s4 = 0;
       for (; s4 < n4 && (!MAIN || 4 * s4 < lead); ++s4) {
-        // (not unrolled: few steps of a long sweep)
+        // (not unrolled: few steps of a long sweep; a halo that unrolls the steps
+        // between takes 35 us of a call of 250 rows x 59,796 columns instead of 24)
         for (int32_t u = 0; u < 4; ++u) step(u, std::true_type{}, s0 + 4 * s4 + u);
         advance();
       }
@@ -386,11 +387,11 @@ __device__ __forceinline__ void sweep(const RowsArgs& a, const RowPack& pk, cons
 // ---------------------------------------------------------------------------
 
 template <class F, int R, bool STREAM, bool DPP>
-__device__ __forceinline__ void halo_body(const RowsArgs& a, const RowClass& cl, int32_t pack,
-                                          int32_t seg, int32_t wave, char* smem) {
+__device__ __forceinline__ void halo_body(const RowsCall& a, const RowClass& cl,
+                                          const RowPack& pk, int32_t pack, int32_t seg,
+                                          int32_t wave, char* smem) {
   using D = Lds<STREAM>;
   char* const lds = smem + wave * D::kBytes;
-  const RowPack pk = get_pack(a, pack);
   const int lane = (int)threadIdx.x & 63;
   const LaneRows w = lane_rows<R, STREAM>(a, pk, lane);
   uint32_t x[R], h[R], sd = 0u;
@@ -465,7 +466,7 @@ __device__ __forceinline__ void halo_body(const RowsArgs& a, const RowClass& cl,
 // One result of `of` that meet in word `at`: true for the last to come, with
 // the smallest key of all.  Atomics alone carry it, so order among them is
 // enough: the minimum has come back before the count goes out.
-__device__ __forceinline__ bool meet(const RowsArgs& a, int64_t at, uint32_t of, uint64_t& key) {
+__device__ __forceinline__ bool meet(const RowsCall& a, int64_t at, uint32_t of, uint64_t& key) {
   const uint64_t old = __hip_atomic_fetch_min(&a.keys[at], key, __ATOMIC_RELAXED,
                                               __HIP_MEMORY_SCOPE_AGENT);
   asm volatile("s_waitcnt vmcnt(0)" ::"v"((uint32_t)old), "v"((uint32_t)(old >> 32)) : "memory");
@@ -475,15 +476,94 @@ __device__ __forceinline__ bool meet(const RowsArgs& a, int64_t at, uint32_t of,
   return true;
 }
 
+// Columns [c0, c1) of a pack.
 template <class F, int R, bool STREAM, bool DPP>
-__device__ __forceinline__ void main_body(const RowsArgs& a, const RowClass& cl, int32_t at,
-                                          int32_t pack, int32_t seg, char* lds) {
-  using D = Lds<STREAM>;
+__device__ __forceinline__ void main_body(const RowsCall& a, const RowClass& cl,
+                                          const RowPack& pk, int32_t pack, int32_t seg, int32_t c0,
+                                          int32_t c1, char* lds,
+                                          uint32_t (&best)[Lds<STREAM>::kPairs],
+                                          int32_t (&bestj)[Lds<STREAM>::kPairs]) {
+  const int lane = (int)threadIdx.x & 63;
+  const LaneRows w = lane_rows<R, STREAM>(a, pk, lane);
+  uint32_t x[R], h[R], sd;
+  load_rows<F, R>(a, w, x);
+  if (c0 > 0) {
+    const uint32_t* b = a.bound + cl.bound_at +
+                        ((int64_t)(pack - cl.first_pack) * (cl.nseg - 1) + (seg - 1)) *
+                            rows_bound_words(R);
+#pragma unroll
+    for (int r = 0; r < R; ++r) h[r] = b[r * 64 + lane];
+    sd = b[R * 64 + lane];
+  } else {
+#pragma unroll
+    for (int r = 0; r < R; ++r) h[r] = F::kInf;
+    sd = w.first && !(STREAM && w.resident) ? 0u : F::kInf;
+  }
+  sweep<F, R, STREAM, DPP, true>(a, pk, w, lds, c0, (c1 - c0 + 3) / 4, c1, x, h, sd, best, bestj);
+}
+
+// f(integral_constant<int, R>) for the class's rows per lane.  DPP: the
+// powers of two alone.
+template <bool DPP, class Fn>
+__device__ __forceinline__ void for_rows(int32_t rows, Fn&& f) {
+#define SDTW_ROWS(R) \
+  case R: f(std::integral_constant<int, R>{}); break;
+  if constexpr (DPP) {
+    switch (rows) { SDTW_ROWS(2) SDTW_ROWS(4) SDTW_ROWS(8) SDTW_ROWS(16) SDTW_ROWS(32) }
+  } else {
+    switch (rows) {
+      SDTW_ROWS(2) SDTW_ROWS(4) SDTW_ROWS(6) SDTW_ROWS(8) SDTW_ROWS(10) SDTW_ROWS(12)
+      SDTW_ROWS(14) SDTW_ROWS(16) SDTW_ROWS(18) SDTW_ROWS(20) SDTW_ROWS(22) SDTW_ROWS(24)
+      SDTW_ROWS(26) SDTW_ROWS(28) SDTW_ROWS(30) SDTW_ROWS(32)
+    }
+  }
+#undef SDTW_ROWS
+}
+
+// (with few classes the arguments are read where they are)
+template <bool DPP>
+using Call = std::conditional_t<DPP, const RowsCall&, const RowsCall>;
+
+template <class F, bool STREAM, bool DPP>
+__global__ __launch_bounds__(64 * kHaloWaves, 4) void k_rows_halo(RowsArgs a) {
+  extern __shared__ __align__(16) char smem[];
+  const int32_t wave = __builtin_amdgcn_readfirstlane((int32_t)threadIdx.x >> 6);
+  const int32_t at = (int32_t)blockIdx.x;
+  int c = 0;
+  for (int k = 1; k < a.nclasses; ++k)
+    if (at >= a.cls[k].first_halo) c = k;
+  const RowClass cl = a.cls[c];
+  const int32_t in = at - cl.first_halo;
+  const int32_t pack = cl.first_pack + in / (cl.nseg - 1), seg = 1 + in % (cl.nseg - 1);
+  Call<DPP> call = a;
   const RowPack pk = get_pack(a, pack);
+  for_rows<DPP>(cl.rows_per_lane, [&](auto rc) {
+    halo_body<F, decltype(rc)::value, STREAM, DPP>(call, cl, pk, pack, seg, wave, smem);
+  });
+}
+
+// A workgroup's waves take consecutive items, mostly segments of one pack,
+// and so end together.
+template <class F, bool STREAM, bool DPP>
+__global__ __launch_bounds__(64 * kMainWaves, 4) void k_rows_main(RowsArgs a) {
+  using D = Lds<STREAM>;
+  extern __shared__ __align__(16) char smem[];
   const int lane = (int)threadIdx.x & 63, half = lane >> 5;
+  const int32_t wave = __builtin_amdgcn_readfirstlane((int32_t)threadIdx.x >> 6);
+  const int32_t at = (int32_t)blockIdx.x * kMainWaves + wave;
+  if (at >= a.nwaves) return;
+  if (a.skip && *a.skip) return;
+  int c = 0;
+  for (int k = 1; k < a.nclasses; ++k)
+    if (at >= a.cls[k].first_wave) c = k;
+  const RowClass cl = a.cls[c];
+  const int32_t in = at - cl.first_wave;
+  const int32_t pack = cl.first_pack + in / cl.nseg, seg = in % cl.nseg;
+  Call<DPP> call = a;
+  const RowPack pk = get_pack(a, pack);
   int32_t nsegs = 1;  // segments this wave covers
   if (cl.nseg > 1) {
-    const uint32_t* f = a.fail + at - seg;
+    const uint32_t* f = call.fail + at - seg;
     if (seg > 0 && f[seg])
       nsegs = 0;  // the wave to the left comes here
     else
@@ -498,24 +578,12 @@ __device__ __forceinline__ void main_body(const RowsArgs& a, const RowClass& cl,
   }
   if (nsegs > 0) {
     const int32_t c0 = seg * cl.segcols;
-    const int32_t c1 = seg + nsegs == cl.nseg ? (int32_t)a.n : (seg + nsegs) * cl.segcols;
-    const LaneRows w = lane_rows<R, STREAM>(a, pk, lane);
-    uint32_t x[R], h[R], sd;
-    load_rows<F, R>(a, w, x);
-    if (c0 > 0) {
-      const uint32_t* b = a.bound + cl.bound_at +
-                          ((int64_t)(pack - cl.first_pack) * (cl.nseg - 1) + (seg - 1)) *
-                              rows_bound_words(R);
-#pragma unroll
-      for (int r = 0; r < R; ++r) h[r] = b[r * 64 + lane];
-      sd = b[R * 64 + lane];
-    } else {
-#pragma unroll
-      for (int r = 0; r < R; ++r) h[r] = F::kInf;
-      sd = w.first && !(STREAM && w.resident) ? 0u : F::kInf;
-    }
-    sweep<F, R, STREAM, DPP, true>(a, pk, w, lds, c0, (c1 - c0 + 3) / 4, c1, x, h, sd, best,
-                                   bestj);
+    const int32_t c1 =
+        seg + nsegs == cl.nseg ? (int32_t)call.n : (seg + nsegs) * cl.segcols;
+    for_rows<DPP>(cl.rows_per_lane, [&](auto rc) {
+      main_body<F, decltype(rc)::value, STREAM, DPP>(call, cl, pk, pack, seg, c0, c1,
+                                                     smem + wave * D::kBytes, best, bestj);
+    });
   }
 #pragma unroll
   for (int k = 0; k < D::kReads; ++k) {
@@ -533,77 +601,23 @@ __device__ __forceinline__ void main_body(const RowsArgs& a, const RowClass& cl,
                             ((int64_t)(pack - cl.first_pack) * D::kReads + k) * (groups + 1);
         if (groups) {
           const int32_t g = seg / kRowsGroup, left = cl.nseg - g * kRowsGroup;
-          write = meet(a, res + 1 + g, left < kRowsGroup ? left : kRowsGroup, key);
+          write = meet(call, res + 1 + g, left < kRowsGroup ? left : kRowsGroup, key);
         }
-        write = write && meet(a, res, groups ? groups : cl.nseg, key);
+        write = write && meet(call, res, groups ? groups : cl.nseg, key);
       }
       if (write) {
         const int32_t item = pk.item[k];
         int32_t out = item;
         if constexpr (STREAM) {
-          const StreamItem it = get_item(a, item);
+          const StreamItem it = get_item(call, item);
           out = it.out;
-          it.acc[a.row_min_at] = (uint32_t)(key >> 32);
+          it.acc[call.row_min_at] = (uint32_t)(key >> 32);
         }
-        F::store_cost(a.cost, out, (uint32_t)(key >> 32));
-        a.end[out] = (int32_t)(uint32_t)key;
+        F::store_cost(call.cost, out, (uint32_t)(key >> 32));
+        call.end[out] = (int32_t)(uint32_t)key;
       }
     }
   }
-}
-
-// f(integral_constant<int, R>) for the class's rows per lane.  DPP: the
-// powers of two alone.
-template <bool DPP, class Fn>
-__device__ __forceinline__ void for_rows(int32_t rows, Fn&& f) {
-#define SDTW_ROWS(R) \
-  case R: f(std::integral_constant<int, R>{}); break;
-  if constexpr (DPP) {
-    switch (rows) { SDTW_ROWS(2) SDTW_ROWS(4) SDTW_ROWS(8) SDTW_ROWS(16) SDTW_ROWS(32) }
-  } else {
-    switch (rows) {
-      SDTW_ROWS(2) SDTW_ROWS(4) SDTW_ROWS(6) SDTW_ROWS(8) SDTW_ROWS(10) SDTW_ROWS(12)
-      SDTW_ROWS(14) SDTW_ROWS(16) SDTW_ROWS(20) SDTW_ROWS(24) SDTW_ROWS(28) SDTW_ROWS(32)
-    }
-  }
-#undef SDTW_ROWS
-}
-
-template <class F, bool STREAM, bool DPP>
-__global__ __launch_bounds__(64 * kHaloWaves, 4) void k_rows_halo(RowsArgs a) {
-  extern __shared__ __align__(16) char smem[];
-  const int32_t wave = __builtin_amdgcn_readfirstlane((int32_t)threadIdx.x >> 6);
-  const int32_t at = (int32_t)blockIdx.x;
-  int c = 0;
-  for (int k = 1; k < a.nclasses; ++k)
-    if (at >= a.cls[k].first_halo) c = k;
-  const RowClass cl = a.cls[c];
-  const int32_t in = at - cl.first_halo;
-  for_rows<DPP>(cl.rows_per_lane, [&](auto rc) {
-    halo_body<F, decltype(rc)::value, STREAM, DPP>(a, cl, cl.first_pack + in / (cl.nseg - 1),
-                                                   1 + in % (cl.nseg - 1), wave, smem);
-  });
-}
-
-// A workgroup's waves take consecutive items, mostly segments of one pack,
-// and so end together.
-template <class F, bool STREAM, bool DPP>
-__global__ __launch_bounds__(64 * kMainWaves, 4) void k_rows_main(RowsArgs a) {
-  extern __shared__ __align__(16) char smem[];
-  const int32_t wave = __builtin_amdgcn_readfirstlane((int32_t)threadIdx.x >> 6);
-  const int32_t at = (int32_t)blockIdx.x * kMainWaves + wave;
-  if (at >= a.nwaves) return;
-  if (a.skip && *a.skip) return;
-  int c = 0;
-  for (int k = 1; k < a.nclasses; ++k)
-    if (at >= a.cls[k].first_wave) c = k;
-  const RowClass cl = a.cls[c];
-  const int32_t in = at - cl.first_wave;
-  for_rows<DPP>(cl.rows_per_lane, [&](auto rc) {
-    main_body<F, decltype(rc)::value, STREAM, DPP>(a, cl, at, cl.first_pack + in / cl.nseg,
-                                                   in % cl.nseg,
-                                                   smem + wave * Lds<STREAM>::kBytes);
-  });
 }
 
 // LDS of a workgroup that leaves a CU no more than its even share of a
