@@ -56,22 +56,18 @@ CUS, SIMDS_PER_CU, CLOCK_GHZ = 256, 4, 2.4
 SIMD_CYCLES_PER_64_CELLS = {"i16": 4 + 4, "f32": 2 + 4 + 2}
 
 
-# HBM bytes per launch of the alignment kernel, from the rocprofv3 FETCH_SIZE
+# HBM bytes per alignment call (halo and sweep), from the rocprofv3 FETCH_SIZE
 # and WRITE_SIZE passes summarised in
-# profiles/counters_k_align_skew_i16_w32_b2_1024xU250-500_vs_9999990.md (mean of
-# the timed dispatches), each scaled by what the counter reads for a plain
-# device copy of known size (factors 1.9998 and 1.0000), keyed by workload and
-# launch shape, valid only while the kernel source is the one measured (sha256
-# of csrc/align.hip); otherwise `traffic` is null.
-_ALIGN_SHA = "e006ed6f05e6ecc5b642142dc28531bbd670e283cc849969bb1d2ed4df42f60c"
+# profiles/counters_k_rows_i16_1024xU250-500_vs_9999990.md (mean of the timed
+# calls), scaled by what the counter reads for a plain device copy of known
+# size (factors 1.9998 and 1.0000), keyed by workload, valid only without a
+# launch shape of the caller's and while the sources that make and cut the
+# launch are the ones measured; otherwise `traffic` is null.
+TRAFFIC_SOURCES = ("rows.h", "cells.h", "api.hip")
 MEASURED_TRAFFIC = {
-    ("1024 reads M~U[250,500] vs 5,000,000-base genome", "i16", 32, 1, 2): {
-        "fetch_bytes": 11427785939, "write_bytes": 320303312, "align_hip_sha256": _ALIGN_SHA},
-    # profiles/counters_k_align_skew_i16_w32_b1_4096x250.md and ..._w32_k2_b1_...
-    ("4096 reads M=250 vs 29,903-base genome", "i16", 32, 1, 1): {
-        "fetch_bytes": 15545467, "write_bytes": 3531545, "align_hip_sha256": _ALIGN_SHA},
-    ("4096 reads M=250 vs 29,903-base genome", "i16", 32, 2, 1): {
-        "fetch_bytes": 15697822, "write_bytes": 3529177, "align_hip_sha256": _ALIGN_SHA},
+    ("1024 reads M~U[250,500] vs 5,000,000-base genome", "i16"): {
+        "fetch_bytes": 5961922724, "write_bytes": 184549920,
+        "sha256": "f4acacafbe6835c061b8447263527d6e8080051993e4ed14f36351d3012e4e8c"},
 }
 
 
@@ -83,16 +79,17 @@ def progress(msg: str):
     print(f"bench [{time.perf_counter() - _T0:7.1f} s] {msg}", file=sys.stderr, flush=True)
 
 
-def measured_traffic(workload: str, dtype: str, cfg: dict):
+def measured_traffic(workload: str, dtype: str, shaped: bool):
     import hashlib
-    key = (workload, dtype, cfg["strip"], cfg["chains"], cfg["bands"])
-    m = MEASURED_TRAFFIC.get(key)
-    if m is None:
+    m = MEASURED_TRAFFIC.get((workload, dtype))
+    if m is None or shaped:
         return None
-    src = os.path.join(ROOT, "paper_2211_07340_amd", "csrc", "align.hip")
-    with open(src, "rb") as f:
-        if hashlib.sha256(f.read()).hexdigest() != m["align_hip_sha256"]:
-            return None
+    h = hashlib.sha256()
+    for name in TRAFFIC_SOURCES:
+        with open(os.path.join(ROOT, "paper_2211_07340_amd", "csrc", name), "rb") as f:
+            h.update(f.read())
+    if h.hexdigest() != m["sha256"]:
+        return None
     return m["fetch_bytes"] + m["write_bytes"]
 
 
@@ -161,7 +158,8 @@ def main():
     offs_dev = torch.from_numpy(reads.offsets).to(dev)
     plan = sd.Plan(reads.offsets, dt)
     tune_ms = None
-    if args.strip or args.chains or args.waves or args.bands or args.band_rows >= 0:
+    shaped = bool(args.strip or args.chains or args.waves or args.bands or args.band_rows >= 0)
+    if shaped:
         plan.set_config(args.strip, args.chains, args.waves, args.bands, args.band_rows)
     elif not args.no_autotune:
         # launch shape picked by the library's autotuner on this batch (on the
@@ -227,7 +225,7 @@ def main():
                      "achieved": round(kern_tcups, 3), "peak": round(peak, 3),
                      "unit": "TCUPS", "frac": round(kern_tcups / peak, 4),
                      "kernel_ms": round(kern_ms, 4),
-                     "traffic": measured_traffic(w.name, args.dtype, pcfg)},
+                     "traffic": measured_traffic(w.name, args.dtype, shaped)},
     }
 
     progress(f"{kern_ms:.2f} ms per alignment launch ({kern_tcups / peak:.3f} of the roof)")

@@ -41,14 +41,15 @@
 //
 // What bounds it, and what it measured (MI355X, against the column-lane
 // kernels of align.hip and the row scan of wide.hip that ran before).  The
-// sweep is bound by VALU issue: 2.05 instructions per 64 cells, of which 2
-// are the cells', at 4.4 cycles each with four waves on a SIMD (int16; bare
-// v_min3_u32 and v_sad_u32 reach 4.5), the rest being clock (2.2-2.35 of the 2.4
-// GHz, 2.0 on float32) and idle lanes.  1,024 reads of 250-500 rows x 9,999,990
-// columns 306 -> 230 ms, 4,096 of 250 x 59,796 in float32 4.14 -> 3.50 ms, 48
-// of 20-300 x 59,796 2.88 -> 0.15 ms, one of 250 x 9,999,990 2.09 -> 0.29 ms and
-// x 59,796 0.53 -> 0.06 ms, two 400-row chunks on 256 resident rows x 9,999,990
-// 339 -> 131 ms, on 4 one by one 26.7 -> 4.4 ms.
+// sweep is bound by VALU issue: 2.02 to 2.05 instructions per 64 cells from 16
+// rows per lane up, of which 2 are the cells', at 4.3 to 4.5 cycles each with
+// three or four waves on a SIMD (int16; bare v_min3_u32 and v_sad_u32 reach
+// 4.5), the rest being clock (2.2-2.35 of the 2.4 GHz, 2.0 on float32) and idle
+// lanes.  1,024 reads of 250-500 rows x 9,999,990 columns 306 -> 224 ms, 4,096 of
+// 250 x 59,796 in float32 4.2 -> 3.4 ms, 8,192 of 100-2,000 x 59,796 34.3 -> 32.5
+// ms, 48 of 20-300 x 59,796 2.88 -> 0.14 ms, one of 250 x 9,999,990 2.09 -> 0.29 ms
+// and x 59,796 0.53 -> 0.06 ms, two 400-row chunks on 256 resident rows x 9,999,990
+// 340 -> 127 ms, on 4 one by one 26.8 -> 4.4 ms.
 #pragma once
 #include <limits.h>
 
@@ -342,7 +343,8 @@ __device__ __forceinline__ void sweep(const RowsCall& a, const RowPack& pk, cons
       int32_t s4 = 0;
       for (; s4 < n4 && (!MAIN || 4 * s4 < lead); ++s4) {
         // (not unrolled: few steps of a long sweep; a halo that unrolls the steps
-        // between takes 35 us of a call of 250 rows x 59,796 columns instead of 24)
+        // between is no faster where halos count: 250 rows x 59,796 columns 62.5 us
+        // a call against 61.9)
         for (int32_t u = 0; u < 4; ++u) step(u, std::true_type{}, s0 + 4 * s4 + u);
         advance();
       }
