@@ -137,6 +137,7 @@ static int cu_count() {
 struct RowLayout {
   std::vector<RowPack> packs;
   std::vector<RowClass> classes;
+  int32_t max_held = 0;  // most rows that a chunk's resident row holds already
 };
 
 // Rows per lane of a read that shares waves with reads like it: those that
@@ -314,7 +315,9 @@ static double rows_cut(RowsArgs& a, const RowLayout& lay, int64_t n, double roun
     work += wave * (double)c.nseg * c.npacks / simds;
     longest = std::max(longest, wave);
     if (c.nseg > 1) {
-      const double h = ((stream ? 1.33 : 1.125) * c.max_m + 64.0) / 4.0 + c.max_lanes;
+      // (a climb of 0.3 of the rows held: 0.05 for a read that fits nowhere,
+      // 0.35 to 0.65 for an on-target read)
+      const double h = (1.125 * c.max_m + 64.0 + 0.3 * lay.max_held) / 4.0 + c.max_lanes;
       halo += h * (double)(c.nseg - 1) * c.npacks / a.nhalo *
               (RowCost{cost.dpp, cost.f32, false}.step(c.rows_per_lane, 4.0) +
                (cost.dpp ? 0.0 : 20.0));
@@ -1074,7 +1077,7 @@ static int64_t one_words(const OneRead& o, int64_t n, int32_t m) {
   return o.words + (o.cols ? wide_scratch_words(n, m, o.cols) : 0) + 1;
 }
 static OneRead one_read(sdtw_ref ref, const void* q, int32_t m, bool stream, int64_t max_words,
-                        void* cost, int32_t* end) {
+                        void* cost, int32_t* end, int32_t held = 0) {
   OneRead o;
   RowsArgs& a = o.rows;
   a.ref = ref->data;
@@ -1082,7 +1085,8 @@ static OneRead one_read(sdtw_ref ref, const void* q, int32_t m, bool stream, int
   a.q = q;
   a.cus = std::max(cu_count(), 1);
   a.single_m = m;
-  const RowLayout lay = rows_layout({{0, m}}, true, 1);
+  RowLayout lay = rows_layout({{0, m}}, true, 1);
+  lay.max_held = held;
   a.pack = lay.packs[0];
   if (ref->n >= kScanBehind) {
     o.cols = wide_pick_cols(ref->n, ref->device);
@@ -1646,6 +1650,8 @@ int sdtw_stream_extend(const sdtw_stream* streams, int32_t ns, const void* chunk
     RowsArgs rb = ra;
     RowLayout lay = rows_layout(chunks, false, kRowsStreamReads);
     RowLayout lay1 = rows_layout(chunks, true, kRowsStreamReads);
+    for (int32_t t = nskew; t < ns; ++t)
+      lay.max_held = lay1.max_held = std::max(lay.max_held, sl.host[t].m_old);
     int64_t words = 0, words1 = 0;
     const double shared = rows_best_cut(ra, lay, false, ref->n, dtype == SDTW_F32, true, INT64_MAX,
                                         &words);
@@ -1770,7 +1776,7 @@ int sdtw_stream_extend_wide(sdtw_stream s, const void* chunk_dev, int32_t M, int
   if (rc) return rc;
   DescSlot& sl = *pick;
   OneRead one;
-  if (rows) one = one_read(ref, chunk_dev, M, true, INT64_MAX, cost_dev, end_dev);
+  if (rows) one = one_read(ref, chunk_dev, M, true, INT64_MAX, cost_dev, end_dev, s->rows);
   rc = ensure_part(sl, rows ? one_words(one, ref->n, M) : wide_scratch_words(ref->n, M, cols));
   if (rc) return rc;
   auto tok = std::make_shared<CallToken>();

@@ -24,6 +24,7 @@ struct FmtI16 {
   __device__ static __forceinline__ void store_cost(void* cost, int32_t r, uint32_t v) {
     ((int32_t*)cost)[r] = (int32_t)v;
   }
+  __device__ static __forceinline__ float value(uint32_t v) { return (float)v; }
 };
 
 struct FmtF32 {
@@ -37,6 +38,7 @@ struct FmtF32 {
   __device__ static __forceinline__ void store_cost(void* cost, int32_t r, uint32_t v) {
     ((float*)cost)[r] = __uint_as_float(v);
   }
+  __device__ static __forceinline__ float value(uint32_t v) { return __uint_as_float(v); }
 };
 
 // f(integral_constant<int, I>) for I in [B, E), unrolled at compile time

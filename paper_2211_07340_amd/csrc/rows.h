@@ -34,10 +34,12 @@
 // the true column lies between the two; where they are equal in every row,
 // that is the true column, and what follows from it is exact.  Paths that
 // start in the halo beat paths that cross all of it after about as many
-// columns as the read has rows (halo_body has the figures); a segment
-// whose column does not settle in three attempts, each twice as far left (a
-// stretch without variation), is left to the wave of the segment to its left,
-// which goes on into it: its own state at the border is exact.
+// columns as the read has rows, or when a row is extended as it takes to
+// climb from the row's minimum to its other costs (halo_body has the figures); a
+// segment whose column does not settle in three attempts, each twice as far
+// left, or in a halo as long as itself (a stretch without variation) is left to
+// the wave of the segment to its left, which goes on into it: its own state at
+// the border is exact.
 //
 // What bounds it, and what it measured (MI355X, against the column-lane
 // kernels of align.hip and the row scan of wide.hip that ran before).  The
@@ -145,7 +147,8 @@ struct LaneRows {
   bool first, last, full;
   int64_t q0;      // query index of the lane's first row
   uint32_t* acc;   // STREAM: the resident row
-  bool resident;   // STREAM: it holds rows already
+  bool resident;   // STREAM: it holds rows already,
+  int32_t held;    // so many
 };
 
 template <int R, bool STREAM>
@@ -171,6 +174,7 @@ __device__ __forceinline__ LaneRows lane_rows(const RowsCall& a, const RowPack& 
     m = it.m;
     w.acc = it.acc;
     w.resident = it.m_old > 0;
+    w.held = it.m_old;
   } else {
     q0 = a.offs ? a.offs[w.item] : 0;
     m = a.offs ? (int32_t)(a.offs[w.item + 1] - q0) : a.single_m;
@@ -404,14 +408,35 @@ __device__ __forceinline__ void halo_body(const RowsCall& a, const RowClass& cl,
     if (w.resident) bound = w.acc[a.row_min_at];
   }
   // Columns until the two recurrences meet, measured on simulated reads: 0.8
-  // to 1.1 M for fresh reads, up to 1.3 M for a chunk that extends as many
-  // rows, more where the resident row's minimum lies far below its other
-  // costs (an on-target read late in its course: 2.6 M).
-  int32_t H = STREAM ? pk.max_m + pk.max_m / 3 + 64 : pk.max_m + pk.max_m / 8 + 32;
+  // to 1.1 M, and for a chunk as many columns again as a path needs to climb
+  // from the resident row's minimum to the row's costs hereabouts, 0.55 to 0.65
+  // held (1 - minimum / cost): nothing for a read that fits nowhere, 700 to 1,300
+  // columns for an on-target read with 2,000 rows held, whatever the chunk.  (On
+  // 59,796 columns in 233 segments every one of 36 chunks of 40, 270 and 400
+  // rows on 400, 2,000 and 3,600 settles at once, at noise of 0.1 to 0.3 sd; with
+  // 0.64 for 0.68 up to 4% try twice, which holds up the sweep.  16 reads with
+  // 2,000 rows held, by 40: 1.77 ms when 1.33 M + 64 columns, doubled twice, left
+  // 98% of the segments to their left neighbours, 0.17 so.)
+  float climb = 0.0f;
+  if constexpr (STREAM) {
+    if (w.resident) {
+      float cost = 0.0f;  // (a segment has at least 64 columns)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) cost += 0.25f * F::value(w.acc[c1 - 1 - 16 * k]);
+      climb = 0.68f * (float)w.held * (1.0f - F::value(bound) / cost);
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) climb = fmaxf(climb, __shfl_xor(climb, off));
+    climb = climb > 0.0f ? fminf(climb, 1e9f) : 0.0f;  // (0 of a row without costs)
+  }
+  int32_t H = pk.max_m + pk.max_m / 8 + 32 +
+              __builtin_amdgcn_readfirstlane((int32_t)climb);
   H = (H + 3) & ~3;
   uint32_t* const sw = (uint32_t*)smem;  // the exchange: (R + 1) words per lane
   bool ok = false;
-  for (int attempt = 0; attempt < 3 && !ok; ++attempt, H *= 2) {
+  // (three times, and on as long as the halo is shorter than the segment that
+  // the wave to the left would walk instead)
+  for (int attempt = 0; !ok && (attempt < 3 || H < cl.segcols); ++attempt) {
     const int32_t c0 = c1 > H ? c1 - H : 0;  // (c1 is a multiple of 4)
     const bool edge = c0 == 0;               // the left edge: +inf is the true column
     const uint32_t before = edge || wave == 1 ? F::kInf : bound;
@@ -438,6 +463,7 @@ __device__ __forceinline__ void halo_body(const RowsCall& a, const RowClass& cl,
     for (int r = 0; r < R; ++r)
       differ |= r < w.nr && sw[r * 64 + lane] != h[r] ? 1u : 0u;
     ok = __syncthreads_or((int)differ) == 0 || edge;
+    H = H < c1 / 2 ? 2 * H : c1;  // (c1: the left edge)
   }
   if (wave == 1) {
     uint32_t* const out = a.bound + cl.bound_at +
