@@ -254,9 +254,11 @@ int sdtw_free_reference(sdtw_ref ref);
  * the same read lengths.  Reads of up to 2,048 rows share waves that hold a
  * few rows of them per lane, and the reference is cut into column segments
  * that are aligned at once, as many as a cost model of the launch finds best
- * for the batch and the reference's length.  Longer reads, and every read of
- * a plan whose launch shape was set (sdtw_plan_set_config), run on the
- * column-lane kernels: ordered longest first and pulled by a persistent grid
+ * for the batch and the reference's length.  Longer reads, every read of
+ * a plan whose launch shape was set (sdtw_plan_set_config), and every read
+ * against a reference of which so much lies in runs of 64 and more equal
+ * values that by the model segments do not pay (from about a tenth on) run on
+ * the column-lane kernels: ordered longest first and pulled by a persistent grid
  * (one launch per group of reads that share a kernel configuration), reads of
  * 64 rows or fewer by the one-wave kernel.
  *
@@ -375,9 +377,9 @@ int sdtw_align_one(sdtw_ref ref, const void* q_dev, int32_t M, void* cost_dev,
  * equal sdtw_align_one's bit for bit; the latency no longer grows with N /
  * (columns of one workgroup).  Reads of up to 2,048 rows with cols = 0 are
  * aligned against many column segments at once; longer reads, any other
- * `cols`, and references of 2^20 columns and more on which most segments'
- * left columns depend on everything to their left (references without
- * variation) by row scans: each of the M rows of Eq. 1 is computed as a prefix
+ * `cols`, and references with long runs of equal values (or of 2^20 columns
+ * and more on which many segments' left columns depend on everything to their
+ * left) by row scans: each of the M rows of Eq. 1 is computed as a prefix
  * scan over the N columns (a row of the recurrence is a composition of maps
  * x -> min(a, x + d), section 4.3 computes the same cells as an oblique
  * wavefront), with tiles of 256 x `cols` columns that pass their boundary
@@ -542,7 +544,8 @@ int sdtw_stream_best_two(const sdtw_stream* streams, int32_t ns, int32_t window,
  * Launch shape of later sdtw_stream_extend calls on streams of `ref` (one
  * chain per lane of the column-lane kernel); ref = NULL sets the process
  * default that references without their own setting use.  With both 0 (the
- * default) chunks of up to 2,048 rows are laid out as sdtw_plan_create does.
+ * default) chunks of up to 2,048 rows are laid out as sdtw_plan_create does,
+ * on the references that it names.
  *   strip  columns per lane, 16 or 32; 0 = 32 for references of 2^20 columns
  *          or more, else 16.
  *   bands  waves per chunk (the row bands of sdtw_plan_set_config), 1 to 4;

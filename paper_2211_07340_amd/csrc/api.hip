@@ -25,6 +25,7 @@ struct sdtw_ref_s {
   int64_t n;       // true length
   int64_t n_pad;   // device layout length
   uint32_t* data;  // u32 biased int16 or float bits
+  int64_t flat;    // columns in runs of at least 64 equal values
   std::atomic<int> open_streams;
   std::atomic<int> stream_strip{0};  // sdtw_stream_set_config for this reference (0: automatic)
   std::atomic<int> stream_bands{0};
@@ -76,6 +77,8 @@ struct sdtw_plan_s {
   uint64_t* scratch;
   int64_t cut_n;                  // reference length that `cut` is for (0: none yet)
   int cut_lay;
+  double cut_cycles;              // modelled
+  double short_rows;              // rows of order[nlong ..) in all
   sdtw::RowsArgs cut;             // how it is cut
 };
 
@@ -368,6 +371,27 @@ static void rows_scratch(RowsArgs& a, uint64_t* s) {
   a.bound = a.fail + (((int64_t)a.nwaves + 1) & ~(int64_t)1);
 }
 
+// Whether reads or chunks of `rows` rows in all leave the row-lane kernel, cut
+// as in `a` (of `cycles` modelled cycles), for the column-lane kernels on n
+// columns of this reference.  Equal values cost a path that stays on a row of about the same
+// value next to nothing, so the column segments that they fill do not settle, and
+// one wave per pack walks them: 48 reads of 250 rows against 1,000,000 equal
+// values 73.7 ms, 22.5 on the column-lane kernels, and with a tenth of the values
+// equal 8.6 and 22.5.  A walked step takes up to 1.4 times the model's; the
+// column-lane kernels take a read's tiles one after another at 50 cycles a column
+// (40 for chunks on long references) or, with many reads, 4,500 cells a cycle.
+static bool walked_longer(sdtw_ref ref, int64_t n, const RowsArgs& a, double cycles, double rows,
+                          bool stream) {
+  if (ref->flat == 0) return false;
+  double step = 0.0;
+  for (int k = 0; k < a.nclasses; ++k)
+    step = std::max(step, RowCost{a.dpp != 0, ref->dtype == SDTW_F32, stream}.step(
+                              a.cls[k].rows_per_lane, 1.0));
+  const double walk = 1.4 / 4.0 * step * (double)ref->flat * (double)n / (double)ref->n;
+  const double tiles = (double)n * (stream && n >= (int64_t(1) << 20) ? 40.0 : 50.0);
+  return cycles + walk > std::max(tiles, rows * (double)n / (4500.0 / 256.0 * a.cus));
+}
+
 static bool valid_strip(int s) { return s == 8 || s == 16 || s == 32; }
 
 }  // namespace sdtw
@@ -643,11 +667,11 @@ int sdtw_load_reference(const void* ref, int64_t n, int dtype, int ref_is_device
   const int64_t n_pad = padded_length(n);
   uint32_t* data = nullptr;
   void* tmp = nullptr;
-  int32_t* nonfinite = nullptr;
-  int32_t host_nonfinite = 0;
+  int32_t* found = nullptr;
+  int32_t host_found[1 + kFlatCounts] = {};  // non-finite values, runs of 64 equal ones
   int rc = check_hip(hipMalloc((void**)&data, (size_t)n_pad * 4), "sdtw_load_reference: alloc");
-  if (!rc) rc = check_hip(hipMalloc((void**)&nonfinite, sizeof(int32_t)), "sdtw_load_reference: alloc");
-  if (!rc) rc = check_hip(hipMemcpyAsync(nonfinite, &host_nonfinite, sizeof(int32_t),
+  if (!rc) rc = check_hip(hipMalloc((void**)&found, sizeof host_found), "sdtw_load_reference: alloc");
+  if (!rc) rc = check_hip(hipMemcpyAsync(found, host_found, sizeof host_found,
                                          hipMemcpyHostToDevice, st), "sdtw_load_reference: copy");
   const void* src = ref;
   if (!rc && !ref_is_device) {
@@ -656,15 +680,15 @@ int sdtw_load_reference(const void* ref, int64_t n, int dtype, int ref_is_device
                             "sdtw_load_reference: copy");
     src = tmp;
   }
-  if (!rc) rc = check_hip(launch_layout_reference(src, n, dtype, data, n_pad, nonfinite, st),
+  if (!rc) rc = check_hip(launch_layout_reference(src, n, dtype, data, n_pad, found, st),
                           "sdtw_load_reference: layout");
-  if (!rc) rc = check_hip(hipMemcpyAsync(&host_nonfinite, nonfinite, sizeof(int32_t),
+  if (!rc) rc = check_hip(hipMemcpyAsync(host_found, found, sizeof host_found,
                                          hipMemcpyDeviceToHost, st), "sdtw_load_reference: copy");
   if (!rc) rc = check_hip(hipStreamSynchronize(st), "sdtw_load_reference: sync");
   if (tmp) (void)hipFree(tmp);
-  if (nonfinite) (void)hipFree(nonfinite);
-  if (!rc && host_nonfinite)
-    rc = set_error(SDTW_EINVAL, "sdtw_load_reference: %d non-finite values", host_nonfinite);
+  if (found) (void)hipFree(found);
+  if (!rc && host_found[0])
+    rc = set_error(SDTW_EINVAL, "sdtw_load_reference: %d non-finite values", host_found[0]);
   if (rc) {
     if (data) (void)hipFree(data);
     return rc;
@@ -679,6 +703,8 @@ int sdtw_load_reference(const void* ref, int64_t n, int dtype, int ref_is_device
   r->n = n;
   r->n_pad = n_pad;
   r->data = data;
+  r->flat = 0;
+  for (int k = 0; k < kFlatCounts; ++k) r->flat += 64 * (int64_t)host_found[1 + k];
   r->open_streams = 0;
   *out = r;
   return SDTW_OK;
@@ -712,10 +738,10 @@ struct LaunchGroup {
   int32_t first, count, max_m, chains, bands, max_band, band_target;
 };
 
-static std::vector<LaunchGroup> launch_groups(const sdtw_plan_s* p) {
+static std::vector<LaunchGroup> launch_groups(const sdtw_plan_s* p, bool rows) {
   std::vector<LaunchGroup> g;
   int32_t pos = 0;
-  const int32_t n = p->rows ? p->nlong : p->nq;  // the rest: the row-lane kernel
+  const int32_t n = rows ? p->nlong : p->nq;  // the rest: the row-lane kernel
   for (int k = p->chains; k >= 1; k /= 2) {
     if (!valid_strip_chains(p->strip, k)) continue;
     const int bands = valid_skew_config(p->strip, k, p->bands) ? p->bands : 1;
@@ -840,6 +866,7 @@ int sdtw_plan_create(const int64_t* offsets_host, int32_t nq, int dtype, sdtw_pl
   std::vector<std::pair<int32_t, int32_t>> reads;
   for (int32_t i = p->nlong; i < nq; ++i)
     reads.emplace_back(order[(size_t)i], p->sorted_m[(size_t)i]);
+  for (const auto& rd : reads) p->short_rows += rd.second;
   for (int i = 0; i < 2; ++i) {
     p->lay[i] = new (std::nothrow) RowLayout(rows_layout(reads, i == 1, kRowsReads));
     if (!p->lay[i]) {
@@ -969,10 +996,32 @@ int sdtw_align_batch(sdtw_ref ref, sdtw_plan plan, const void* q_dev, void* cost
   return align_batch_impl(ref, plan, q_dev, cost_dev, end_dev, (hipStream_t)stream, ref->n);
 }
 
+// Cuts the plan's reads of up to kRowsMaxM rows for n columns of ref; false if
+// they are better off on the column-lane kernels there.
+static bool plan_cut(sdtw_ref ref, sdtw_plan plan, int64_t n) {
+  if (plan->nlong == plan->nq) return true;
+  if (plan->cut_n != n) {
+    const bool f32 = plan->dtype == SDTW_F32;
+    RowsArgs ra{}, rb{};
+    ra.cus = rb.cus = plan->cus;
+    int64_t words = 0;
+    const double shared = rows_best_cut(ra, *plan->lay[0], false, n, f32, false,
+                                        plan->scratch_words, &words);
+    const double alone = rows_best_cut(rb, *plan->lay[1], true, n, f32, false,
+                                       plan->scratch_words, &words);
+    plan->cut_lay = alone < shared;
+    plan->cut = plan->cut_lay ? rb : ra;
+    plan->cut_cycles = plan->cut_lay ? alone : shared;
+    plan->cut_n = n;
+  }
+  return !walked_longer(ref, n, plan->cut, plan->cut_cycles, plan->short_rows, false);
+}
+
 static int align_batch_impl(sdtw_ref ref, sdtw_plan plan, const void* q_dev, void* cost_dev,
                             int32_t* end_dev, hipStream_t st, int64_t n) {
   SDTW_REQUIRE(valid_strip(plan->strip), "sdtw_align_batch: bad strip");
-  const std::vector<LaunchGroup> groups = launch_groups(plan);
+  const bool rows = plan->rows && plan_cut(ref, plan, n);
+  const std::vector<LaunchGroup> groups = launch_groups(plan, rows);
   const size_t lds_max = (size_t)max_lds_bytes();
   for (const LaunchGroup& g : groups) {
     const size_t lds = g.chains ? skew_lds_bytes(plan->strip, g.chains, g.bands, g.max_band)
@@ -1008,19 +1057,7 @@ static int align_batch_impl(sdtw_ref ref, sdtw_plan plan, const void* q_dev, voi
     }
     if (rc) return rc;
   }
-  if (plan->rows && plan->nlong < plan->nq) {
-    if (plan->cut_n != n) {
-      const bool f32 = plan->dtype == SDTW_F32;
-      RowsArgs ra{}, rb{};
-      ra.cus = rb.cus = plan->cus;
-      int64_t words = 0;
-      const double shared = rows_best_cut(ra, *plan->lay[0], false, n, f32, false,
-                                          plan->scratch_words, &words);
-      plan->cut_lay = rows_best_cut(rb, *plan->lay[1], true, n, f32, false, plan->scratch_words,
-                                    &words) < shared;
-      plan->cut = plan->cut_lay ? rb : ra;
-      plan->cut_n = n;
-    }
+  if (rows && plan->nlong < plan->nq) {
     RowsArgs ra = plan->cut;
     ra.ref = ref->data;
     ra.n = n;
@@ -1058,14 +1095,16 @@ int sdtw_align_one(sdtw_ref ref, const void* q_dev, int32_t M, void* cost_dev, i
 }
 
 // One read of m <= kRowsMaxM rows, or a chunk of them that extends `row`,
-// spread over the device: the row-lane kernel with one read to a wave and,
-// behind it on long references, the row scan for references on which most
-// segments stay unsettled (without variation over thousands of columns), where
-// a single wave would walk them: 0.3 s instead of 2 ms for 250 rows x 10 M
-// equal values.  The scan's kernels end at once otherwise (about 8 us), so
-// shorter references, which one wave walks in milliseconds, go without.
+// spread over the device: the row-lane kernel with one read to a wave, unless
+// the reference has so many columns without variation that the wave that walks
+// them takes longer than the row scan.  250 rows against equal values: 1.74 ms
+// walked and 0.54 scanned on 59,796 columns, 25.7 and 0.75 on 1,000,000; a
+// fiftieth of 1,000,000 equal: 0.69 and 0.75.  Behind it on long references
+// stands the row scan for segments that stay unsettled for another reason; its
+// kernels end at once otherwise (about 8 us, too much for a call on a shorter
+// reference).
 struct OneRead {
-  bool fits = false;  // the scratch allows it
+  bool fits = false;  // the scratch allows it, and the row scan is not faster
   RowsArgs rows{};
   int cols = 0;       // of the row scan, 0: none
   int64_t words = 0;  // scratch of the row-lane kernel (the row scan's follows)
@@ -1092,11 +1131,18 @@ static OneRead one_read(sdtw_ref ref, const void* q, int32_t m, bool stream, int
     o.cols = wide_pick_cols(ref->n, ref->device);
     max_words -= wide_scratch_words(ref->n, m, o.cols) + 1;
   }
-  o.fits = rows_best_cut(a, lay, true, ref->n, false, stream, max_words, &o.words) >= 0.0;
+  // cycles: a step of one wave on a SIMD per four columns, and the row scan
+  // (fitted to 59,796 to 9,999,990 columns x 40 to 400 rows, within a quarter)
+  const double walk = 0.25 * (double)ref->flat *
+                      RowCost{true, false, stream}.step(lay.classes[0].rows_per_lane, 1.0);
+  const double scan = 60000.0 + m * (5000.0 + 0.0015 * (double)ref->n);
+  o.fits = rows_best_cut(a, lay, true, ref->n, false, stream, max_words, &o.words) >= 0.0 &&
+           walk <= scan;
   if (!a.nhalo) o.cols = 0;
   a.cost = cost;
   a.end = end;
   a.row_min_at = ref->n_pad - 1;
+  a.far = ref->flat == 0;
   return o;
 }
 static hipError_t launch_one(sdtw_ref ref, OneRead& o, uint64_t* scratch, hipStream_t st,
@@ -1132,7 +1178,7 @@ int sdtw_align_one_wide(sdtw_ref ref, const void* q_dev, int32_t M, int cols, vo
   SDTW_REQUIRE(cols == 0 || cols == 8 || cols == 16 || cols == 32 || cols == 64,
                "sdtw_align_one_wide: cols=%d not in {0, 8, 16, 32, 64}", cols);
   if (int rc = require_device(ref->device, "sdtw_align_one_wide")) return rc;
-  const bool rows = cols == 0 && M <= kRowsMaxM;
+  const bool may_rows = cols == 0 && M <= kRowsMaxM;
   if (cols == 0) cols = wide_pick_cols(ref->n, ref->device);
   SDTW_REQUIRE(wide_tiles(ref->n, cols) <= (int64_t)INT32_MAX,
                "sdtw_align_one_wide: reference too long for %d columns per thread", cols);
@@ -1144,7 +1190,8 @@ int sdtw_align_one_wide(sdtw_ref ref, const void* q_dev, int32_t M, int cols, vo
   if (rc) return rc;
   DescSlot& sl = *pick;
   OneRead one;
-  if (rows) one = one_read(ref, q_dev, M, false, INT64_MAX, cost_dev, end_dev);
+  if (may_rows) one = one_read(ref, q_dev, M, false, INT64_MAX, cost_dev, end_dev);
+  const bool rows = one.fits;
   rc = ensure_part(sl, rows ? one_words(one, ref->n, M) : wide_scratch_words(ref->n, M, cols));
   if (rc) return rc;
   auto tok = std::make_shared<CallToken>();
@@ -1317,12 +1364,13 @@ int sdtw_plan_autotune(sdtw_ref ref, sdtw_plan plan, const void* q_dev, void* co
   // (the row-lane kernel takes reads of up to kRowsMaxM rows and has no shape to
   // tune: without longer reads there is nothing to time)
   plan->rows = true;
+  const bool nothing = plan->nlong == 0 && plan_cut(ref, plan, n);
   std::vector<TuneVal> cand;
   const int32_t median_m = plan->sorted_m[plan->sorted_m.size() / 2];
   for (int strip : {16, 32})
     for (int chains : {1, 2})
       for (int bands : {1, 2, 3, 4}) {
-        if (plan->nlong == 0) continue;
+        if (nothing) continue;
         if (!valid_skew_config(strip, chains, bands)) continue;
         if (bands > 1 && plan->max_m < bands * skew_min_m(chains)) continue;
         std::vector<int32_t> targets = {0};
@@ -1607,12 +1655,45 @@ int sdtw_stream_extend(const sdtw_stream* streams, int32_t ns, const void* chunk
   if (kStrip == 0) kStrip = g_stream_strip.load();
   if (kStrip == 0) kStrip = ref->n >= (int64_t(1) << 20) ? 32 : 16;
   // The row-lane kernel takes chunks of up to kRowsMaxM rows, unless a launch
-  // shape was set; order[nskew ..) are its chunks.
+  // shape was set or it does not suit the reference; order[nskew ..) are its chunks.
   const bool shaped = ref->stream_bands.load() || g_stream_bands.load() ||
                       ref->stream_strip.load() || g_stream_strip.load();
   int32_t nskew = ns;
   if (!shaped)
     for (nskew = 0; nskew < ns && len(order[(size_t)nskew]) > kRowsMaxM;) ++nskew;
+  RowsArgs ra{};
+  RowLayout lay;
+  int64_t words = 0;
+  if (nskew < ns) {
+    std::vector<std::pair<int32_t, int32_t>> chunks;
+    double rows = 0.0;
+    int32_t held = 0;
+    for (int32_t t = nskew; t < ns; ++t) {
+      chunks.emplace_back(t, (int32_t)len(order[(size_t)t]));
+      rows += (double)chunks.back().second;
+      held = std::max(held, streams[order[(size_t)t]]->rows);
+    }
+    ra.cus = cus;
+    RowsArgs rb = ra;
+    lay = rows_layout(chunks, false, kRowsStreamReads);
+    RowLayout lay1 = rows_layout(chunks, true, kRowsStreamReads);
+    lay.max_held = lay1.max_held = held;
+    int64_t words1 = 0;
+    double cycles = rows_best_cut(ra, lay, false, ref->n, dtype == SDTW_F32, true, INT64_MAX,
+                                  &words);
+    const double alone = rows_best_cut(rb, lay1, true, ref->n, dtype == SDTW_F32, true, INT64_MAX,
+                                       &words1);
+    if (alone < cycles) {
+      lay = std::move(lay1);
+      ra = rb;
+      words = words1;
+      cycles = alone;
+    }
+    if (walked_longer(ref, ref->n, ra, cycles, rows, true)) {
+      nskew = ns;
+      lay = RowLayout{};
+    }
+  }
   int32_t nbig = 0, max_band = 0;
   while (nbig < nskew && len(order[(size_t)nbig]) >= skew_min_m(kChains)) {
     max_band = std::max(max_band, skew_band_rows((int32_t)len(order[(size_t)nbig]), kChains, bands));
@@ -1640,27 +1721,8 @@ int sdtw_stream_extend(const sdtw_stream* streams, int32_t ns, const void* chunk
     it.out = i;
     it.pad = 0;
   }
-  RowsArgs ra{};
-  size_t npacks = 0;
-  if (nskew < ns) {
-    std::vector<std::pair<int32_t, int32_t>> chunks;
-    for (int32_t t = nskew; t < ns; ++t)
-      chunks.emplace_back(t, (int32_t)len(order[(size_t)t]));
-    ra.cus = cus;
-    RowsArgs rb = ra;
-    RowLayout lay = rows_layout(chunks, false, kRowsStreamReads);
-    RowLayout lay1 = rows_layout(chunks, true, kRowsStreamReads);
-    for (int32_t t = nskew; t < ns; ++t)
-      lay.max_held = lay1.max_held = std::max(lay.max_held, sl.host[t].m_old);
-    int64_t words = 0, words1 = 0;
-    const double shared = rows_best_cut(ra, lay, false, ref->n, dtype == SDTW_F32, true, INT64_MAX,
-                                        &words);
-    if (rows_best_cut(rb, lay1, true, ref->n, dtype == SDTW_F32, true, INT64_MAX, &words1) < shared) {
-      lay = std::move(lay1);
-      ra = rb;
-      words = words1;
-    }
-    npacks = lay.packs.size();
+  const size_t npacks = lay.packs.size();
+  if (npacks) {
     rc = ensure_part(sl, std::max<int64_t>(1, words));
     if (rc) return rc;
     rows_scratch(ra, sl.part);
@@ -1673,6 +1735,7 @@ int sdtw_stream_extend(const sdtw_stream* streams, int32_t ns, const void* chunk
     ra.cost = cost_dev;
     ra.end = end_dev;
     ra.row_min_at = ref->n_pad - 1;
+    ra.far = ref->flat == 0;
   }
   auto tok = std::make_shared<CallToken>();
   tok->ev = event_get();
@@ -1764,7 +1827,7 @@ int sdtw_stream_extend_wide(sdtw_stream s, const void* chunk_dev, int32_t M, int
   SDTW_REQUIRE(cols == 0 || cols == 8 || cols == 16 || cols == 32 || cols == 64,
                "sdtw_stream_extend_wide: cols=%d not in {0, 8, 16, 32, 64}", cols);
   if (int rc = require_device(ref->device, "sdtw_stream_extend_wide")) return rc;
-  const bool rows = cols == 0 && M <= kRowsMaxM;
+  const bool may_rows = cols == 0 && M <= kRowsMaxM;
   if (cols == 0) cols = wide_pick_cols(ref->n, ref->device);
   SDTW_REQUIRE(wide_tiles(ref->n, cols) <= (int64_t)INT32_MAX,
                "sdtw_stream_extend_wide: reference too long for %d columns per thread", cols);
@@ -1776,7 +1839,8 @@ int sdtw_stream_extend_wide(sdtw_stream s, const void* chunk_dev, int32_t M, int
   if (rc) return rc;
   DescSlot& sl = *pick;
   OneRead one;
-  if (rows) one = one_read(ref, chunk_dev, M, true, INT64_MAX, cost_dev, end_dev, s->rows);
+  if (may_rows) one = one_read(ref, chunk_dev, M, true, INT64_MAX, cost_dev, end_dev, s->rows);
+  const bool rows = one.fits;
   rc = ensure_part(sl, rows ? one_words(one, ref->n, M) : wide_scratch_words(ref->n, M, cols));
   if (rc) return rc;
   auto tok = std::make_shared<CallToken>();

@@ -100,8 +100,11 @@ int64_t ref_scratch_doubles(int64_t n);  // doubles of scratch for n signal valu
 hipError_t launch_prepare_queries(const float* raw, const int64_t* offs, int32_t nq,
                                   double scale, const double* stats_in, double* stats_out,
                                   float* z, int16_t* codes, int64_t* nsat, hipStream_t st);
+// Adds to found[0] the non-finite values, and to found[1 .. kFlatCounts], whose
+// sum counts, the runs of 64 equal values.
+constexpr int kFlatCounts = 31;
 hipError_t launch_layout_reference(const void* src, int64_t n, int dtype,
-                                   uint32_t* dst, int64_t n_pad, int32_t* nonfinite,
+                                   uint32_t* dst, int64_t n_pad, int32_t* found,
                                    hipStream_t st);
 
 // ---- launchers (align.hip) --------------------------------------------------
@@ -230,6 +233,7 @@ struct RowsCall {
   int32_t* end;
   int64_t row_min_at;       // stream: index of the word behind a resident row that holds its
                             // minimum
+  int32_t far;              // stream: halos of up to a segment are worth trying
   StreamItem item;
 };
 struct RowsArgs : RowsCall {

@@ -538,22 +538,26 @@ __global__ __launch_bounds__(64) void k_prep_queries(const float* __restrict__ r
 }
 
 // Device layout of a reference: int16 -> u32 with +32768 bias, float -> bits;
-// zero padding up to n_pad.  Non-finite float values are counted.
+// zero padding up to n_pad (a multiple of the workgroup).  Counted: non-finite
+// float values, and the waves whose 64 values are equal.
 __global__ void k_layout(const void* __restrict__ src, int64_t n, int dtype,
-                         uint32_t* __restrict__ dst, int64_t n_pad, int32_t* __restrict__ nonfinite) {
+                         uint32_t* __restrict__ dst, int64_t n_pad, int32_t* __restrict__ found) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n_pad) return;
   uint32_t v = 0;
   if (i < n) {
     if (dtype == SDTW_I16) {
       v = (uint32_t)((int32_t)((const int16_t*)src)[i] + (int32_t)kI16Bias);
     } else {
       const float f = ((const float*)src)[i];
-      if (!isfinite(f)) atomicAdd(nonfinite, 1);
+      if (!isfinite(f)) atomicAdd(&found[0], 1);
       v = __float_as_uint(f);
     }
   }
   dst[i] = v;
+  const uint32_t v0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
+  const bool equal = __ballot(i < n && v == v0) == ~0ull;
+  // (several words: a constant reference's waves would queue at one)
+  if (equal && (threadIdx.x & 63) == 0) atomicAdd(&found[1 + blockIdx.x % kFlatCounts], 1);
 }
 
 inline unsigned grid_for(int64_t n, int threads) {
@@ -593,9 +597,9 @@ hipError_t launch_prepare_queries(const float* raw, const int64_t* offs, int32_t
 }
 
 hipError_t launch_layout_reference(const void* src, int64_t n, int dtype, uint32_t* dst,
-                                   int64_t n_pad, int32_t* nonfinite, hipStream_t st) {
+                                   int64_t n_pad, int32_t* found, hipStream_t st) {
   hipLaunchKernelGGL(k_layout, dim3(grid_for(n_pad, kPrepThreads)), dim3(kPrepThreads), 0, st,
-                     src, n, dtype, dst, n_pad, nonfinite);
+                     src, n, dtype, dst, n_pad, found);
   return hipGetLastError();
 }
 

@@ -37,7 +37,7 @@
 // columns as the read has rows, or when a row is extended as it takes to
 // climb from the row's minimum to its other costs (halo_body has the figures); a
 // segment whose column does not settle in three attempts, each twice as far
-// left, or in a halo as long as itself (a stretch without variation) is left to
+// left (a stretch without variation; more attempts for chunks), is left to
 // the wave of the segment to its left, which goes on into it: its own state at
 // the border is exact.
 //
@@ -434,9 +434,12 @@ __device__ __forceinline__ void halo_body(const RowsCall& a, const RowClass& cl,
   H = (H + 3) & ~3;
   uint32_t* const sw = (uint32_t*)smem;  // the exchange: (R + 1) words per lane
   bool ok = false;
-  // (three times, and on as long as the halo is shorter than the segment that
-  // the wave to the left would walk instead)
-  for (int attempt = 0; !ok && (attempt < 3 || H < cl.segcols); ++attempt) {
+  // (three times, and for a chunk on a reference without runs of equal values as
+  // long as the halo is shorter than the segment that the wave to the left would
+  // walk instead; where such runs are, tries in vain would take 16 chunks of 400 on
+  // 9,999,990 columns, a fiftieth of them equal, from 24 to 40 ms)
+  for (int attempt = 0; !ok && (attempt < 3 || (STREAM && a.far && H < cl.segcols));
+       ++attempt) {
     const int32_t c0 = c1 > H ? c1 - H : 0;  // (c1 is a multiple of 4)
     const bool edge = c0 == 0;               // the left edge: +inf is the true column
     const uint32_t before = edge || wave == 1 ? F::kInf : bound;
