@@ -14,6 +14,8 @@
 #include <limits.h>
 #include <math.h>
 
+#include <type_traits>
+
 #include "common.h"
 
 namespace sdtw {
@@ -231,29 +233,37 @@ __device__ __forceinline__ int take_runs(double& s, int32_t e, bool ok, SumMap m
   return runs;
 }
 
-// buf[0 .. n) added to s one by one: the chain of additions, with the
-// next 16 values on their way from LDS.
-__device__ __forceinline__ double add_plain(const float* buf, int n, double s) {
-  float4 next[4];
+// buf[0 .. n) added to s one by one: the chain of additions, with the next 16
+// values on their way from LDS.
+__device__ __forceinline__ double add_all(const float4& v, double s) {
+  s += (double)v.x;
+  s += (double)v.y;
+  s += (double)v.z;
+  return s + (double)v.w;
+}
+__device__ __forceinline__ double add_all(const double2& v, double s) {
+  s += v.x;
+  return s + v.y;
+}
+template <class T>
+__device__ __forceinline__ double add_plain(const T* buf, int n, double s) {
+  using V = std::conditional_t<sizeof(T) == 4, float4, double2>;
+  constexpr int kVecs = (int)(16 * sizeof(T) / sizeof(V));
+  V next[kVecs];
   auto fetch = [&](int at) {
-    at = at < kSumTile - 16 ? at : kSumTile - 16;
+    const V* const from = (const V*)(buf + (at < kSumTile - 16 ? at : kSumTile - 16));
 #pragma unroll
-    for (int k = 0; k < 4; ++k) next[k] = *(const float4*)(buf + at + 4 * k);
+    for (int k = 0; k < kVecs; ++k) next[k] = from[k];
   };
   fetch(0);
   int at = 0;
   for (; at + 16 <= n; at += 16) {
-    float4 now[4];
+    V now[kVecs];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) now[k] = next[k];
+    for (int k = 0; k < kVecs; ++k) now[k] = next[k];
     fetch(at + 16);
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      s += (double)now[k].x;
-      s += (double)now[k].y;
-      s += (double)now[k].z;
-      s += (double)now[k].w;
-    }
+    for (int k = 0; k < kVecs; ++k) s = add_all(now[k], s);
   }
   for (; at < n; ++at) s += (double)buf[at];
   return s;
@@ -521,6 +531,35 @@ __global__ __launch_bounds__(64) void k_sum_walk(const float* __restrict__ x, in
   }
 }
 
+// Both sums by one wave, term by term: a few thousand values do not pay for the
+// ten launches of the parallel sums, and so close to zero the sums cross a
+// binade every few runs (preparing 2,000 bases: 77 us term by term, 98 in
+// parallel; 1,000: 44 and 84; 500: 33 to 42 and 76).
+constexpr int64_t kSmallSum = 5 * kSumTile;
+__global__ __launch_bounds__(64) void k_sum_small(const float* __restrict__ x, int32_t n,
+                                                  double* __restrict__ stats,
+                                                  int64_t* __restrict__ nsat) {
+  __shared__ __align__(16) double buf[kSumTile];
+  auto sum = [&](auto&& term_of) {
+    double s = 0.0;
+    for (int32_t a = 0; a < n; a += kSumTile) {
+      const int32_t len = a + kSumTile < n ? kSumTile : n - a;
+      __syncthreads();
+      for (int32_t i = (int32_t)threadIdx.x; i < len; i += 64) buf[i] = term_of(x[a + i]);
+      __syncthreads();
+      s = add_plain(buf, len, s);
+    }
+    return s;
+  };
+  const double mean = sum([](float v) { return term<false>(v, 0.0); }) / (double)n;
+  const double squares = sum([&](float v) { return term<true>(v, mean); });
+  if (threadIdx.x == 0) {
+    stats[0] = mean;
+    stats[1] = sqrt(squares / (double)n);
+    if (nsat) *nsat = 0;
+  }
+}
+
 template <bool SQUARES>
 void launch_sum(const float* x, int64_t n, double* scratch, int64_t* nsat, hipStream_t st) {
   const int32_t ntiles = (int32_t)((n + kSumTile - 1) / kSumTile);
@@ -619,8 +658,13 @@ hipError_t launch_prepare_reference(const uint8_t* g, int64_t L, const float* ta
   hipLaunchKernelGGL(k_kmer, dim3(grid_for(n, kPrepThreads)), dim3(kPrepThreads), 0, st,
                      g, L, k, table, z);
   double* stats = scratch;
-  launch_sum<false>(z, n, scratch, nullptr, st);
-  launch_sum<true>(z, n, scratch, nsat, st);
+  if (n <= kSmallSum) {
+    hipLaunchKernelGGL(k_sum_small, dim3(1), dim3(64), 0, st, z, (int32_t)n, stats,
+                       nsat);
+  } else {
+    launch_sum<false>(z, n, scratch, nullptr, st);
+    launch_sum<true>(z, n, scratch, nsat, st);
+  }
   hipLaunchKernelGGL(k_normalize, dim3(grid_for(n, kPrepThreads)), dim3(kPrepThreads), 0, st,
                      z, n, stats, scale, z, codes, nsat);
   return hipGetLastError();
