@@ -862,7 +862,7 @@ int sdtw_align_one(sdtw_ref ref, const void* q_dev, int32_t M, void* cost_dev, i
 // kernels end at once otherwise (about 8 us, too much for a call on a shorter
 // reference).
 struct OneRead {
-  bool fits = false;  // the scratch allows it, and the row scan is not faster
+  bool fits = false;  // the row scan is not faster
   RowsArgs rows{};
   int cols = 0;       // of the row scan, 0: none
   int64_t words = 0;  // scratch of the row-lane kernel (the row scan's follows)
@@ -894,7 +894,8 @@ static OneRead one_read(sdtw_ref ref, const void* q, int32_t m, bool stream, int
   const double walk = 0.25 * (double)ref->flat *
                       RowCost{true, false, stream}.step(lay.classes[0].rows_per_lane, 1.0);
   const double scan = 60000.0 + m * (5000.0 + 0.0015 * (double)ref->n);
-  o.fits = rows_best_cut(a, lay, true, ref->n, false, stream, max_words, &o.words) >= 0.0 &&
+  // (a cut of three times the scan's time: the scratch allows too few segments)
+  o.fits = rows_best_cut(a, lay, true, ref->n, false, stream, max_words, &o.words) <= 3.0 * scan &&
            walk <= scan;
   if (!a.nhalo) o.cols = 0;
   a.cost = cost;

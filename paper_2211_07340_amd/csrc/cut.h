@@ -122,9 +122,11 @@ struct RowCost {
 // lane end together when columns are dealt out by rows and this.
 constexpr double kRowsStepOver = 2.2;
 
-// Most waves of a SIMD a launch is cut into, one after another or at once:
-// the bound of the scratch that its boundary columns need.
-constexpr int kRowsRounds[] = {1, 2, 3, 4, 6, 8, 12, 16};
+// Waves of a SIMD that a launch is cut into, one after another or at once.  0: one
+// segment per pack, without halo and scratch, where the reads' rows make up much
+// of the reference (512 reads of 2,000 rows x 4,000 columns: 877 us in two
+// segments, 578 in one).
+constexpr int kRowsRounds[] = {0, 1, 2, 3, 4, 6, 8, 12, 16};
 
 // Cuts the reference of n columns into segments for every class so that each
 // SIMD gets `rounds` waves of about equal work (or as many as there are
@@ -137,7 +139,8 @@ static double rows_cut(RowsArgs& a, const RowLayout& lay, int64_t n, double roun
     const double cols = 4.0 * (tau / (c.rows_per_lane + kRowsStepOver) - c.max_lanes);
     const int64_t least = std::max<int64_t>(64, c.max_m / 4);
     const int64_t whole = (n + 63) & ~(int64_t)63;
-    return std::min(whole, (std::max(least, (int64_t)std::min(cols, 2e9)) + 63) & ~(int64_t)63);
+    return std::min(whole, (std::max(least, (int64_t)std::min(cols, (double)whole)) + 63) &
+                               ~(int64_t)63);
   };
   auto count = [&](double tau) {
     int64_t w = 0;
@@ -207,14 +210,18 @@ static double rows_cut(RowsArgs& a, const RowLayout& lay, int64_t n, double roun
                                  : std::max(work, longest * std::ceil(per));
   // A halo is two waves, and the launch takes about one more (1.0 to 1.3 at 2
   // to 30 rows per lane x 1 to 7 waves per SIMD): it ends with those that try
-  // again.
-  halo *= std::max(2.0 * a.nhalo / simds, 1.0) + (cost.dpp ? 1.0 : 1.3);
+  // again and with the fullest SIMDs.  (With rows handed on in registers, long halos
+  // few enough for SIMDs of their own take little more than one: 7 of 2,000 rows 466
+  // us a call, 421 modelled, 707 with a wave more.)
+  const double waves = 2.0 * a.nhalo / simds;
+  const double more = cost.dpp ? std::min(halo, std::max(halo * waves, 8000.0)) : 1.3 * halo;
+  halo = halo * std::max(waves, 1.0) + more;
   return sweep + halo + (a.nhalo ? 35000.0 : 20000.0);
 }
 
-// The best of the cuts with scratch of at most most_words words (its modelled
-// cycles, or -1 if none has), and whether to hand rows on in registers (packs
-// of one read, `alone`).
+// The best of the cuts with scratch of at most most_words words (one segment per
+// pack needs none), its modelled cycles, and whether to hand rows on in registers
+// (packs of one read, `alone`).
 static double rows_best_cut(RowsArgs& a, const RowLayout& lay, bool alone, int64_t n, bool f32,
                             bool stream, int64_t most_words, int64_t* words) {
   double best = -1.0;

@@ -106,9 +106,15 @@ int main() {
         a.cus = cus;
         int64_t words = 0;
         const double t = rows_best_cut(a, lay, alone, n, f32, stream, most, &words);
-        if (t < 0.0) continue;  // (no cut with so little scratch)
-        CHECK(words <= most || !a.nhalo);
+        CHECK(t > 0.0 && words <= most);
         check_cut(a, lay, n, stream, words);
+        // one segment per pack is always to be had, and none better is passed over
+        RowsArgs b{};
+        b.cus = cus;
+        const double uncut = rows_best_cut(b, lay, alone, n, f32, stream, 0, &words);
+        CHECK(b.nhalo == 0 && words == 0 && b.nwaves == (int32_t)lay.packs.size());
+        check_cut(b, lay, n, stream, 0);
+        CHECK(t <= uncut);
       }
     }
   }
