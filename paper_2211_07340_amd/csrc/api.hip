@@ -626,20 +626,14 @@ int sdtw_plan_create(const int64_t* offsets_host, int32_t nq, int dtype, sdtw_pl
     reads.emplace_back(order[(size_t)i], p->sorted_m[(size_t)i]);
   for (const auto& rd : reads) p->short_rows += rd.second;
   for (int i = 0; i < 2; ++i) {
+    if (i == 1 && !alone_pays(*p->lay[0], p->cus)) break;
     p->lay[i] = new (std::nothrow) RowLayout(rows_layout(reads, i == 1, kRowsReads));
     if (!p->lay[i]) {
       delete p->lay[0];
       delete p;
       return set_error(SDTW_ENOMEM, "sdtw_plan_create: host allocation");
     }
-    // the longest reference is cut into the most segments
-    for (int rounds : kRowsRounds) {
-      RowsArgs ra{};
-      ra.cus = p->cus;
-      int64_t w = 0;
-      (void)rows_cut(ra, *p->lay[i], INT32_MAX, rounds, RowCost{}, false, &w);
-      p->scratch_words = std::max(p->scratch_words, w);
-    }
+    p->scratch_words = std::max(p->scratch_words, rows_most_words(*p->lay[i], p->cus));
   }
   int rc = check_hip(hipMalloc((void**)&p->offs_dev, sizeof(int64_t) * (size_t)(nq + 1)),
                      "sdtw_plan_create: alloc");
@@ -651,16 +645,19 @@ int sdtw_plan_create(const int64_t* offsets_host, int32_t nq, int dtype, sdtw_pl
                                     hipMemcpyHostToDevice), "sdtw_plan_create: copy");
   if (!rc) rc = check_hip(hipMemcpy(p->order_dev, order.data(), sizeof(int32_t) * (size_t)nq,
                                     hipMemcpyHostToDevice), "sdtw_plan_create: copy");
-  for (int i = 0; i < 2 && !rc && !reads.empty(); ++i) {
+  for (int i = 0; i < 2 && !rc && !reads.empty() && p->lay[i]; ++i) {
     const size_t bytes = sizeof(RowPack) * p->lay[i]->packs.size();
     rc = check_hip(hipMalloc((void**)&p->packs_dev[i], bytes), "sdtw_plan_create: alloc");
     if (!rc)
       rc = check_hip(hipMemcpy(p->packs_dev[i], p->lay[i]->packs.data(), bytes,
                                hipMemcpyHostToDevice), "sdtw_plan_create: copy");
   }
-  if (!rc && p->scratch_words)
-    rc = check_hip(hipMalloc((void**)&p->scratch, sizeof(uint64_t) * (size_t)p->scratch_words),
-                   "sdtw_plan_create: alloc");
+  if (!rc && p->scratch_words &&
+      hipMalloc((void**)&p->scratch, sizeof(uint64_t) * (size_t)p->scratch_words) != hipSuccess) {
+    (void)hipGetLastError();
+    p->scratch = nullptr;
+    p->scratch_words = 0;  // one segment per pack
+  }
   if (rc) {
     (void)plan_free(p);
     return rc;
@@ -765,8 +762,9 @@ static bool plan_cut(sdtw_ref ref, sdtw_plan plan, int64_t n) {
     int64_t words = 0;
     const double shared = rows_best_cut(ra, *plan->lay[0], false, n, f32, false,
                                         plan->scratch_words, &words);
-    const double alone = rows_best_cut(rb, *plan->lay[1], true, n, f32, false,
-                                       plan->scratch_words, &words);
+    const double alone = plan->lay[1] ? rows_best_cut(rb, *plan->lay[1], true, n, f32, false,
+                                                      plan->scratch_words, &words)
+                                      : INFINITY;
     plan->cut_lay = alone < shared;
     plan->cut = plan->cut_lay ? rb : ra;
     plan->cut_cycles = plan->cut_lay ? alone : shared;

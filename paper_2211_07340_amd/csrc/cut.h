@@ -127,6 +127,12 @@ constexpr double kRowsStepOver = 2.2;
 // of the reference (512 reads of 2,000 rows x 4,000 columns: 877 us in two
 // segments, 578 in one).
 constexpr int kRowsRounds[] = {0, 1, 2, 3, 4, 6, 8, 12, 16};
+// More than four pay where the packs' last, shorter segments are a good part of
+// the waves; few packs have equal waves already (22 packs are cut in 4 rounds, 86
+// in 6, 300 in 16), and their scratch stays small.
+static bool rounds_pay(int rounds, const RowLayout& lay) {
+  return rounds <= 4 || (int64_t)lay.packs.size() >= 12 * (int64_t)rounds;
+}
 
 // Cuts the reference of n columns into segments for every class so that each
 // SIMD gets `rounds` waves of about equal work (or as many as there are
@@ -228,6 +234,7 @@ static double rows_best_cut(RowsArgs& a, const RowLayout& lay, bool alone, int64
   RowsArgs at = a;
   for (int dpp = 0; dpp <= (alone ? 1 : 0); ++dpp) {
     for (int rounds : kRowsRounds) {
+      if (!rounds_pay(rounds, lay)) continue;
       int64_t w = 0;
       const double t = rows_cut(at, lay, n, rounds, RowCost{dpp != 0, f32, stream}, stream, &w);
       if (w > most_words && at.nhalo) continue;
@@ -244,6 +251,28 @@ static double rows_best_cut(RowsArgs& a, const RowLayout& lay, bool alone, int64
     }
   }
   return best;
+}
+// The scratch (64-bit words) for the cuts of a batch that are tried on references
+// of any length, at most kMostPlanWords (1,024 reads of 250 to 500 rows x 10 M
+// columns in 16 rounds take 8.9 M).
+constexpr int64_t kMostPlanWords = 10 << 20;
+static int64_t rows_most_words(const RowLayout& lay, int cus) {
+  int64_t most = 0;
+  for (int rounds : kRowsRounds) {
+    if (!rounds_pay(rounds, lay)) continue;
+    RowsArgs a{};
+    a.cus = cus;
+    int64_t w = 0;
+    (void)rows_cut(a, lay, INT32_MAX - 2 * kPadUnit, rounds, RowCost{}, false, &w);
+    most = std::max(most, w);
+  }
+  // (on some shorter references rounding gives a class a few segments more)
+  return std::min(most + most / 8, kMostPlanWords);
+}
+// Whether reads alone in their waves are worth a layout: not with four waves of
+// shared ones for every SIMD.
+static bool alone_pays(const RowLayout& shared, int cus) {
+  return (int64_t)shared.packs.size() < 16 * (int64_t)cus;
 }
 // The parts of the scratch of a cut launch.
 static void rows_scratch(RowsArgs& a, uint64_t* s) {

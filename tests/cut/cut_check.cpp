@@ -115,8 +115,27 @@ int main() {
         CHECK(b.nhalo == 0 && words == 0 && b.nwaves == (int32_t)lay.packs.size());
         check_cut(b, lay, n, stream, 0);
         CHECK(t <= uncut);
+        // a plan's scratch holds the cuts that are tried, or is at its bound
+        const int64_t plan_words = rows_most_words(lay, cus);
+        CHECK(plan_words <= kMostPlanWords);
+        if (!stream && plan_words < kMostPlanWords) {
+          RowsArgs c{};
+          c.cus = cus;
+          CHECK(rows_best_cut(c, lay, alone, n, f32, false, INT64_MAX, &words) ==
+                rows_best_cut(c, lay, alone, n, f32, false, plan_words, &words));
+        }
       }
     }
+  }
+  // scratch does not grow with reads that fill the device by themselves
+  for (int32_t m : {250, 2000}) {
+    Reads one(1, {0, m}), many;
+    for (int32_t i = 0; i < 65536; ++i) many.emplace_back(i, m);
+    const RowLayout few = rows_layout(one, true, kRowsReads);
+    const RowLayout all = rows_layout(many, false, kRowsReads);
+    CHECK(rows_most_words(few, 256) <= (m == 250 ? 1 << 20 : 5 << 20));
+    CHECK(rows_most_words(all, 256) == 0);
+    CHECK(!alone_pays(all, 256));
   }
   printf("ok %d\n", g_case);
   return 0;
