@@ -126,10 +126,10 @@ constexpr double kRowsStepOver = 2.2;
 // segment per pack, without halo and scratch, where the reads' rows make up much
 // of the reference (512 reads of 2,000 rows x 4,000 columns: 877 us in two
 // segments, 578 in one).
-constexpr int kRowsRounds[] = {0, 1, 2, 3, 4, 6, 8, 12};
+constexpr int kRowsRounds[] = {0, 1, 2, 3, 4, 6, 8, 12, 16};
 // More than four pay where the packs' last, shorter segments are a good part of
 // the waves; few packs have equal waves already (22 packs are cut in 4 rounds, 86
-// in 6, 300 in 12), and their scratch stays small.
+// in 6, 300 in 16), and their scratch stays small.
 static bool rounds_pay(int rounds, const RowLayout& lay) {
   return rounds <= 4 || (int64_t)lay.packs.size() >= 12 * (int64_t)rounds;
 }
@@ -192,7 +192,7 @@ static double rows_cut(RowsArgs& a, const RowLayout& lay, int64_t n, double roun
   // about how far the longest wave exceeds the mean, or the last round's gap.
   // Each pack's last segment is shorter than the others, so many rounds of
   // short waves fill the SIMDs better than one (1,024 reads of 250 to 500
-  // rows x 10 M columns: 248 ms with 4, 231 with 8, 225 with 12, 227.5 with 16).  A launch
+  // rows x 10 M columns: 248 ms with 4, 231 with 8, 224 with 16).  A launch
   // takes about 8 us besides its steps.
   const double simds = 4.0 * a.cus, per = a.nwaves / simds;
   double work = 0.0, longest = 0.0, halo = 0.0;
@@ -254,7 +254,7 @@ static double rows_best_cut(RowsArgs& a, const RowLayout& lay, bool alone, int64
 }
 // The scratch (64-bit words) for the cuts of a batch that are tried on references
 // of any length, at most kMostPlanWords (1,024 reads of 250 to 500 rows x 10 M
-// columns in 12 rounds take 5.9 M, 2,000-row reads 11).
+// columns in 16 rounds take 8.9 M).
 constexpr int64_t kMostPlanWords = 10 << 20;
 static int64_t rows_most_words(const RowLayout& lay, int cus) {
   int64_t most = 0;
