@@ -254,8 +254,8 @@ static double rows_best_cut(RowsArgs& a, const RowLayout& lay, bool alone, int64
 }
 // The scratch (64-bit words) for the cuts of a batch that are tried on references
 // of any length, at most kMostPlanWords (1,024 reads of 250 to 500 rows x 10 M
-// columns in 16 rounds take 8.9 M).
-constexpr int64_t kMostPlanWords = 10 << 20;
+// columns in 16 rounds take 11.9 M, and 224 ms; in 12 rounds 227).
+constexpr int64_t kMostPlanWords = 12 << 20;
 static int64_t rows_most_words(const RowLayout& lay, int cus) {
   int64_t most = 0;
   for (int rounds : kRowsRounds) {
