@@ -392,7 +392,7 @@ int sdtw_align_one(sdtw_ref ref, const void* q_dev, int32_t M, void* cost_dev,
  *          measured for each reference length).
  *   cost_dev  out int32[1]; end_dev out int32[1] (0-based column).
  * Enqueues two to five kernels and records an event that tracks the reuse of
- * its library-owned scratch (8 MiB per call in flight unless more is needed:
+ * its library-owned scratch (64 MiB per call in flight unless more is needed:
  * 8 bytes per tile per row for the row scan, 4 bytes per row and segment), so
  * the call is not for graph capture.  If a
  * tile waits for its left neighbour for about a second (a defect; never in
@@ -490,6 +490,11 @@ int sdtw_stream_copy_row(sdtw_stream s, void* dst_dev, void* stream);
  * CU once the calls in flight, the library counts its own, cover more than half
  * the CUs, and take CUs of their own below that.)  Placement never changes
  * results.
+ * Each call in flight (up to 64 per device, counting sdtw_stream_extend_wide,
+ * sdtw_align_one_wide and sdtw_stream_best_two) uses 64 MiB of library-owned
+ * device scratch, outside the row budget: allocated by the first call that finds
+ * none free, kept until the process ends, and not grown by this call; without
+ * memory for it the reference is not cut into segments.
  */
 int sdtw_stream_extend(const sdtw_stream* streams, int32_t ns, const void* chunk_dev,
                        const int64_t* chunk_offsets_host, void* cost_dev, int32_t* end_dev,
@@ -533,8 +538,8 @@ int sdtw_stream_extend_wide(sdtw_stream s, const void* chunk_dev, int32_t M, int
  * that wrote the rows (same stream).  Closing a stream waits for this call.
  * SDTW_ESTATE if a stream has no rows yet; EINVAL if ns times
  * ceil(n / 16384) exceeds INT32_MAX.  Uses library-owned device scratch of
- * 8 bytes per 16,384 columns per row: 8 MiB per call in flight, allocated
- * by the first such call; a call that needs more reallocates, which waits
+ * 8 bytes per 16,384 columns per row, from the 64 MiB per call in flight that
+ * sdtw_stream_extend uses too; a call that needs more reallocates, which waits
  * for all work on the device.
  */
 int sdtw_stream_best_two(const sdtw_stream* streams, int32_t ns, int32_t window,

@@ -205,7 +205,8 @@ struct DescSlot {
   RowPack* host_packs() { return (RowPack*)(host + cap); }
   RowPack* dev_packs() { return (RowPack*)(dev + cap); }
   int32_t* counter() { return (int32_t*)((char*)dev + kPer * (size_t)cap); }
-  uint64_t* part = nullptr;  // sdtw_stream_best_two: per-segment minima
+  uint64_t* part = nullptr;  // scratch of the call: per-segment minima (sdtw_stream_best_two),
+                             // boundary columns and results, flags of a row scan
   int64_t part_cap = 0;
   std::shared_ptr<CallToken> last;
 };
@@ -243,19 +244,20 @@ static int ensure_slot(DescSlot& sl, int32_t n) {
   return SDTW_OK;
 }
 
-// Segment minima of sdtw_stream_best_two.  The first allocation already
-// holds 2^20 keys (8 MiB: e.g. 1,024 rows of 16 M columns), so that serving
-// loops do not regrow it: hipFree of the old buffer would wait for all work
-// on the device, including long launches on other HIP streams.
-constexpr int64_t kMinPartKeys = int64_t(1) << 20;
+// A slot's scratch.  The first allocation already holds 2^23 words (64 MiB), and
+// sdtw_stream_extend cuts its launches to fit, so that serving loops do not regrow
+// it: hipFree of the old buffer would wait for all work on the device, including
+// long launches on other HIP streams.  (256 chunks of 400 rows x 10 M columns take
+// 32 MB, 1,024 of them 63; segment minima 8 MB for 1,024 rows of 16 M columns.)
+constexpr int64_t kPartWords = int64_t(1) << 23;
 static int ensure_part(DescSlot& sl, int64_t n) {
   if (sl.part_cap >= n) return SDTW_OK;
-  const int64_t cap = std::max<int64_t>(std::max<int64_t>(n, 2 * sl.part_cap), kMinPartKeys);
+  const int64_t cap = std::max<int64_t>(std::max<int64_t>(n, 2 * sl.part_cap), kPartWords);
   if (sl.part) (void)hipFree(sl.part);
   sl.part = nullptr;
   sl.part_cap = 0;
   int rc = check_hip(hipMalloc((void**)&sl.part, sizeof(uint64_t) * (size_t)cap),
-                     "sdtw_stream_best_two: segment minima");
+                     "scratch of a call");
   if (rc) return rc;
   sl.part_cap = cap;
   return SDTW_OK;
@@ -1436,9 +1438,9 @@ int sdtw_stream_extend(const sdtw_stream* streams, int32_t ns, const void* chunk
     RowLayout lay1 = rows_layout(chunks, true, kRowsStreamReads);
     lay.max_held = lay1.max_held = held;
     int64_t words1 = 0;
-    double cycles = rows_best_cut(ra, lay, false, ref->n, dtype == SDTW_F32, true, INT64_MAX,
+    double cycles = rows_best_cut(ra, lay, false, ref->n, dtype == SDTW_F32, true, kPartWords,
                                   &words);
-    const double alone = rows_best_cut(rb, lay1, true, ref->n, dtype == SDTW_F32, true, INT64_MAX,
+    const double alone = rows_best_cut(rb, lay1, true, ref->n, dtype == SDTW_F32, true, kPartWords,
                                        &words1);
     if (alone < cycles) {
       lay = std::move(lay1);
@@ -1480,8 +1482,10 @@ int sdtw_stream_extend(const sdtw_stream* streams, int32_t ns, const void* chunk
   }
   const size_t npacks = lay.packs.size();
   if (npacks) {
-    rc = ensure_part(sl, std::max<int64_t>(1, words));
-    if (rc) return rc;
+    if (words && ensure_part(sl, words)) {  // no memory for it: one segment per pack
+      (void)hipGetLastError();
+      rows_best_cut(ra, lay, false, ref->n, dtype == SDTW_F32, true, 0, &words);
+    }
     rows_scratch(ra, sl.part);
     std::copy(lay.packs.begin(), lay.packs.end(), sl.host_packs());
     ra.ref = ref->data;
