@@ -198,12 +198,13 @@ static RowPool* pool_for(int dev) {
 // ---- pinned descriptor slots for stream_extend -----------------------------
 struct DescSlot {
   StreamItem* host = nullptr;
-  StreamItem* dev = nullptr;  // cap items, as many packs, then one int32 work counter
+  StreamItem* dev = nullptr;  // room for cap items and packs, then one int32 work counter
   int32_t cap = 0;
-  // (on the host likewise: the packs follow cap items)
+  // (on the host likewise; a call's packs follow its n items, so that one copy
+  // takes just those)
   static constexpr size_t kPer = sizeof(StreamItem) + sizeof(RowPack);
-  RowPack* host_packs() { return (RowPack*)(host + cap); }
-  RowPack* dev_packs() { return (RowPack*)(dev + cap); }
+  RowPack* host_packs(int32_t n) { return (RowPack*)(host + n); }
+  RowPack* dev_packs(int32_t n) { return (RowPack*)(dev + n); }
   int32_t* counter() { return (int32_t*)((char*)dev + kPer * (size_t)cap); }
   uint64_t* part = nullptr;  // scratch of the call: per-segment minima (sdtw_stream_best_two),
                              // boundary columns and results, flags of a row scan
@@ -1487,12 +1488,12 @@ int sdtw_stream_extend(const sdtw_stream* streams, int32_t ns, const void* chunk
       rows_best_cut(ra, lay, false, ref->n, dtype == SDTW_F32, true, 0, &words);
     }
     rows_scratch(ra, sl.part);
-    std::copy(lay.packs.begin(), lay.packs.end(), sl.host_packs());
+    std::copy(lay.packs.begin(), lay.packs.end(), sl.host_packs(ns));
     ra.ref = ref->data;
     ra.n = ref->n;
     ra.q = chunk_dev;
     ra.items = sl.dev;
-    ra.packs = sl.dev_packs();
+    ra.packs = sl.dev_packs(ns);
     ra.cost = cost_dev;
     ra.end = end_dev;
     ra.row_min_at = ref->n_pad - 1;
@@ -1502,10 +1503,9 @@ int sdtw_stream_extend(const sdtw_stream* streams, int32_t ns, const void* chunk
   tok->ev = event_get();
   if (!tok->ev) return set_error(SDTW_EDEVICE, "sdtw_stream_extend: event creation failed");
   hipStream_t st = (hipStream_t)stream;
-  // the items and, behind the slot's capacity of them, the packs
-  const size_t desc = npacks ? sizeof(StreamItem) * (size_t)sl.cap + sizeof(RowPack) * npacks
-                             : sizeof(StreamItem) * (size_t)ns;
-  rc = check_hip(hipMemcpyAsync(sl.dev, sl.host, desc, hipMemcpyHostToDevice, st),
+  rc = check_hip(hipMemcpyAsync(sl.dev, sl.host,
+                                sizeof(StreamItem) * (size_t)ns + sizeof(RowPack) * npacks,
+                                hipMemcpyHostToDevice, st),
                  "sdtw_stream_extend: descriptors");
   AlignArgs a{};
   a.ref = ref->data;

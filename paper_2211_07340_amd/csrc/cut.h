@@ -50,21 +50,42 @@ static int rows_alone(int32_t m) {
 static RowLayout rows_layout(const std::vector<std::pair<int32_t, int32_t>>& reads, bool alone,
                              int max_reads) {
   RowLayout out;
-  std::vector<int> rows(reads.size());
-  for (size_t i = 0; i < reads.size(); ++i)
-    rows[i] = alone ? rows_alone(reads[i].second) : rows_to_share(reads[i].second, max_reads);
+  // the reads class by class, longest first: so in a class those of a number of
+  // lanes follow one another, most lanes first
+  std::vector<uint8_t> kind(reads.size());
+  std::vector<int32_t> of(reads.size());
+  int32_t count[kRowsClasses + 1] = {};
+  int32_t m = 0;
+  int at = 0;
+  for (size_t i = 0; i < reads.size(); ++i) {
+    if (reads[i].second != m) {
+      m = reads[i].second;
+      const int R = alone ? rows_alone(m) : rows_to_share(m, max_reads);
+      at = (int)(std::find(kRowsPerLane, kRowsPerLane + kRowsClasses, R) - kRowsPerLane);
+    }
+    kind[i] = (uint8_t)at;
+    ++count[at + 1];
+  }
+  for (int k = 0; k < kRowsClasses; ++k) count[k + 1] += count[k];
+  int32_t next[kRowsClasses];
+  std::copy(count, count + kRowsClasses, next);
+  for (size_t i = 0; i < reads.size(); ++i) of[(size_t)next[kind[i]]++] = (int32_t)i;
   if (alone) max_reads = 1;
+  if (alone) out.packs.reserve(reads.size());
   for (int k = kRowsClasses - 1; k >= 0; --k) {
+    if (count[k] == count[k + 1]) continue;
     const int R = kRowsPerLane[k];
-    // by lanes: the reads that take that many, longest last
-    std::vector<std::vector<std::pair<int32_t, int32_t>>> by(kLanes + 1);
-    for (size_t i = reads.size(); i-- > 0;)
-      if (rows[i] == R) by[rows_lanes(reads[i].second, R)].push_back(reads[i]);
+    int32_t head[kLanes + 1] = {}, end[kLanes + 1] = {};  // the reads of l lanes: of[head, end)
+    for (int32_t i = count[k]; i < count[k + 1]; ++i) {
+      const int32_t l = rows_lanes(reads[(size_t)of[(size_t)i]].second, R);
+      if (end[l] == 0) head[l] = i;
+      end[l] = i + 1;
+    }
     RowClass c{};
     c.rows_per_lane = R;
     c.first_pack = (int32_t)out.packs.size();
     for (int top = kLanes; top >= 1;) {
-      if (by[top].empty()) {
+      if (head[top] == end[top]) {
         --top;
         continue;
       }
@@ -72,10 +93,9 @@ static RowLayout rows_layout(const std::vector<std::pair<int32_t, int32_t>>& rea
       int32_t room = kLanes;
       while (p.nreads < max_reads && room > 0) {
         int l = std::min(room, top);
-        while (l >= 1 && by[l].empty()) --l;
+        while (l >= 1 && head[l] == end[l]) --l;
         if (l < 1) break;
-        const auto rd = by[l].back();
-        by[l].pop_back();
+        const auto& rd = reads[(size_t)of[(size_t)head[l]++]];
         p.item[p.nreads] = rd.first;
         p.lane0[p.nreads] = kLanes - room;
         ++p.nreads;
@@ -89,7 +109,7 @@ static RowLayout rows_layout(const std::vector<std::pair<int32_t, int32_t>>& rea
       out.packs.push_back(p);
     }
     c.npacks = (int32_t)out.packs.size() - c.first_pack;
-    if (c.npacks) out.classes.push_back(c);
+    out.classes.push_back(c);
   }
   return out;
 }
