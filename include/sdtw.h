@@ -408,12 +408,14 @@ int sdtw_align_one_wide(sdtw_ref ref, const void* q_dev, int32_t M, int cols, vo
  * hipMalloc): the same kernels, arguments and results, but the scratch is a
  * fixed array of 2^20 64-bit words (8 MiB) that the library holds on every
  * device it runs on until the process ends, and the call records no event.
- * It calls no hipMalloc, hipFree or allocating routine; the first call on a
- * device looks the array's address up once.
+ * It allocates nothing, on the device or the host; the first call on a device
+ * looks the array's address up once.
  *   Limit, whichever way the read is aligned: 2 M t + M ceil(t / 64) + t + 1 for t =
  *   ceil(N / (256 cols)) tiles must not exceed 2^20 (EINVAL otherwise, with
  *   the sizes in the message; nothing is launched).  For example M = 250
- *   fits up to about 16 M columns at cols = 32.
+ *   fits up to about 16 M columns at cols = 32.  Reads of 1,025 to 2,048 rows
+ *   on references of 2^20 columns and more are aligned by row scans: the array
+ *   does not hold both the scan's words and enough segments.
  *   Every call on a device shares that device's array, which keeps the last
  *   call's contents (each call clears what it needs itself, with a kernel):
  *   calls that overlap in time on one device race and must be ordered by

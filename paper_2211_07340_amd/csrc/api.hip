@@ -883,9 +883,8 @@ static OneRead one_read(sdtw_ref ref, const void* q, int32_t m, bool stream, int
   a.q = q;
   a.cus = std::max(cu_count(), 1);
   a.single_m = m;
-  RowLayout lay = rows_layout({{0, m}}, true, 1);
+  RowLayout lay = one_layout(m, &a.pack);
   lay.max_held = held;
-  a.pack = lay.packs[0];
   if (ref->n >= kScanBehind) {
     o.cols = wide_pick_cols(ref->n, ref->device);
     max_words -= wide_scratch_words(ref->n, m, o.cols) + 1;

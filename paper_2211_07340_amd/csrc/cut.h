@@ -15,7 +15,8 @@ namespace sdtw {
 // rows per lane first.
 struct RowLayout {
   std::vector<RowPack> packs;
-  std::vector<RowClass> classes;
+  int32_t nclasses = 0;
+  RowClass classes[kRowsClasses];
   int32_t max_held = 0;  // most rows that a chunk's resident row holds already
 };
 
@@ -109,8 +110,25 @@ static RowLayout rows_layout(const std::vector<std::pair<int32_t, int32_t>>& rea
       out.packs.push_back(p);
     }
     c.npacks = (int32_t)out.packs.size() - c.first_pack;
-    out.classes.push_back(c);
+    out.classes[out.nclasses++] = c;
   }
+  return out;
+}
+// One read of m rows, alone in its wave: the pack goes to *pack, and nothing is
+// allocated.
+static RowLayout one_layout(int32_t m, RowPack* pack) {
+  RowLayout out;
+  RowClass& c = out.classes[out.nclasses++];
+  c = RowClass{};
+  c.rows_per_lane = rows_alone(m);
+  c.npacks = 1;
+  c.max_m = m;
+  c.max_lanes = rows_lanes(m, c.rows_per_lane);
+  *pack = RowPack{};
+  pack->nreads = 1;
+  pack->max_lanes = c.max_lanes;
+  pack->max_m = m;
+  for (int j = 1; j <= kRowsReads; ++j) pack->lane0[j] = c.max_lanes;
   return out;
 }
 
@@ -170,7 +188,8 @@ static double rows_cut(RowsArgs& a, const RowLayout& lay, int64_t n, double roun
   };
   auto count = [&](double tau) {
     int64_t w = 0;
-    for (const RowClass& c : lay.classes) {
+    for (int k = 0; k < lay.nclasses; ++k) {
+      const RowClass& c = lay.classes[k];
       const int64_t cols = columns(c, tau);
       w += c.npacks * ((n + cols - 1) / cols);
     }
@@ -183,11 +202,11 @@ static double rows_cut(RowsArgs& a, const RowLayout& lay, int64_t n, double roun
     (count(mid) > room ? lo : hi) = mid;
   }
   const double tau = count(lo) > room ? hi : lo;
-  a.nclasses = (int32_t)lay.classes.size();
+  a.nclasses = lay.nclasses;
   a.nwaves = a.nhalo = 0;
   int64_t bound = 0, results = 0;
   for (int k = 0; k < a.nclasses; ++k) {
-    RowClass c = lay.classes[(size_t)k];
+    RowClass c = lay.classes[k];
     const int64_t cols = columns(c, tau), s = (n + cols - 1) / cols;
     c.nseg = (int32_t)s;
     c.segcols = (int32_t)cols;

@@ -4,7 +4,9 @@
 // keeps to its scratch.  Prints "ok <cases>" or the first that fails.
 #include <stdio.h>
 #include <stdlib.h>
+#include <string.h>
 
+#include <new>
 #include <random>
 
 #include "../../paper_2211_07340_amd/csrc/cut.h"
@@ -12,6 +14,15 @@
 using namespace sdtw;
 
 static int g_case = 0;
+static long g_allocations = 0;
+void* operator new(size_t n) {
+  ++g_allocations;
+  void* p = malloc(n);
+  if (!p) abort();
+  return p;
+}
+void operator delete(void* p) noexcept { free(p); }
+void operator delete(void* p, size_t) noexcept { free(p); }
 #define CHECK(cond)                                                        \
   do {                                                                     \
     if (!(cond)) {                                                         \
@@ -25,7 +36,8 @@ using Reads = std::vector<std::pair<int32_t, int32_t>>;
 static void check_layout(const RowLayout& lay, const Reads& reads, int max_reads) {
   std::vector<int> seen(reads.size(), 0);
   int32_t pack = 0, last = 33;
-  for (const RowClass& c : lay.classes) {
+  for (int k = 0; k < lay.nclasses; ++k) {
+    const RowClass& c = lay.classes[k];
     CHECK(c.rows_per_lane < last);
     last = c.rows_per_lane;
     CHECK(c.first_pack == pack && c.npacks >= 1);
@@ -49,7 +61,7 @@ static void check_layout(const RowLayout& lay, const Reads& reads, int max_reads
 
 static void check_cut(const RowsArgs& a, const RowLayout& lay, int64_t n, bool stream,
                       int64_t words) {
-  CHECK(a.nclasses == (int32_t)lay.classes.size());
+  CHECK(a.nclasses == lay.nclasses);
   int64_t waves = 0, halos = 0, bound = 0, results = 0;
   for (int k = 0; k < a.nclasses; ++k) {
     const RowClass& c = a.cls[k];
@@ -126,6 +138,21 @@ int main() {
         }
       }
     }
+  }
+  // one read alone: the layout of a batch of one, without an allocation
+  for (int32_t m = 1; m <= kRowsMaxM; ++m) {
+    const RowLayout batch = rows_layout({{0, m}}, true, 1);
+    g_allocations = 0;
+    RowPack pack;
+    const RowLayout one = one_layout(m, &pack);
+    RowsArgs a{};
+    a.cus = 256;
+    int64_t words = 0;
+    (void)rows_best_cut(a, one, true, 1000 * (int64_t)m, false, false, INT64_MAX, &words);
+    CHECK(g_allocations == 0);
+    CHECK(one.nclasses == 1 && batch.nclasses == 1);
+    CHECK(memcmp(&one.classes[0], &batch.classes[0], sizeof(RowClass)) == 0);
+    CHECK(memcmp(&pack, &batch.packs[0], sizeof pack) == 0);
   }
   // scratch does not grow with reads that fill the device by themselves
   for (int32_t m : {250, 2000}) {
