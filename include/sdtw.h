@@ -322,7 +322,9 @@ int sdtw_plan_get_config(sdtw_plan plan, int* strip, int* chains, int* bands,
  * and remember it for sdtw_plan_use_tuned, keyed by the device's
  * architecture and compute units, the dtype, the reference length and the
  * batch's shape class (number of reads, median and longest read length,
- * each in quarter-octave buckets: round(4 log2 v)).  If the environment
+ * each in quarter-octave buckets: round(4 log2 v), at most 43 for the longest of
+ * a plan without reads over 2,048 rows; what was not timed replaces no shape that
+ * was).  If the environment
  * variable SDTW_TUNE_CACHE names a file, tuned shapes are also written there
  * (one per line, the file rewritten after every autotune) and read back by
  * the first sdtw_plan_autotune or sdtw_plan_use_tuned of a process.

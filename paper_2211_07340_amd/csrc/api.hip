@@ -1045,9 +1045,13 @@ std::string device_arch(int device) {
   return a;
 }
 
+// (a plan without reads over kRowsMaxM rows keeps to the buckets below that of
+// kRowsMaxM, so that it shares none with plans whose long reads were timed)
 TuneKey tune_key(const sdtw_plan_s* p, int64_t n) {
+  int max_b = quarter_octave(p->max_m);
+  if (p->nlong == 0) max_b = std::min(max_b, quarter_octave(kRowsMaxM) - 1);
   return {device_arch(p->device), p->cus, p->dtype, n, quarter_octave(p->nq),
-          quarter_octave(p->sorted_m[p->sorted_m.size() / 2]), quarter_octave(p->max_m)};
+          quarter_octave(p->sorted_m[p->sorted_m.size() / 2]), max_b};
 }
 
 // Optional persistence: SDTW_TUNE_CACHE names a text file with one tuned
@@ -1199,7 +1203,11 @@ int sdtw_plan_autotune(sdtw_ref ref, sdtw_plan plan, const void* q_dev, void* co
   const TuneKey key = tune_key(plan, ref->n);
   std::lock_guard<std::mutex> g(g_tune_mu);
   tune_file_read_locked();
-  g_tuned[key] = best;
+  // what was not timed replaces nothing
+  if (!cand.empty())
+    g_tuned[key] = best;
+  else if (!g_tuned.emplace(key, best).second)
+    return SDTW_OK;
   tune_file_write_locked();
   return SDTW_OK;
 }
