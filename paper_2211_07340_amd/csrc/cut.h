@@ -226,19 +226,21 @@ static double rows_cut(RowsArgs& a, const RowLayout& lay, int64_t n, double roun
   a.nresults = results;
   *words = a.nhalo ? results + (results + 1) / 2 + ((int64_t)a.nwaves + 1) / 2 + (bound + 1) / 2
                    : 0;
-  // The sweep: up to four waves of a SIMD run side by side and the fullest
-  // SIMD ends last; more follow one another, and what is left at the end is
-  // about how far the longest wave exceeds the mean, or the last round's gap.
+  // The sweep: up to four waves of a SIMD (chunks: fewer, see rows_side_by_side) run
+  // side by side and the fullest SIMD ends last; more follow one another, and what
+  // is left at the end is about how far the longest wave exceeds the mean, or the
+  // last round's gap.
   // Each pack's last segment is shorter than the others, so many rounds of
   // short waves fill the SIMDs better than one (1,024 reads of 250 to 500
   // rows x 10 M columns: 248 ms with 4, 231 with 8, 224 with 16).  A launch
   // takes about 8 us besides its steps.
   const double simds = 4.0 * a.cus, per = a.nwaves / simds;
+  const double side = rows_side_by_side(stream, cost.f32, a.cls[0].rows_per_lane);
   double work = 0.0, longest = 0.0, halo = 0.0;
   for (int k = 0; k < a.nclasses; ++k) {
     const RowClass& c = a.cls[k];
     const double steps = c.segcols / 4.0 + c.max_lanes;
-    const double wave = steps * cost.step(c.rows_per_lane, std::ceil(per));
+    const double wave = steps * cost.step(c.rows_per_lane, std::min(std::ceil(per), side));
     work += wave * (double)c.nseg * c.npacks / simds;
     longest = std::max(longest, wave);
     if (c.nseg > 1) {
@@ -251,7 +253,7 @@ static double rows_cut(RowsArgs& a, const RowLayout& lay, int64_t n, double roun
     }
   }
   const double mean = work / per;
-  const double sweep = per > 4.0 ? work + std::max(longest - mean, 0.5 * (std::ceil(per) - per) * mean)
+  const double sweep = per > side ? work + std::max(longest - mean, 0.5 * (std::ceil(per) - per) * mean)
                                  : std::max(work, longest * std::ceil(per));
   // A halo is two waves, and the launch takes about one more (1.0 to 1.3 at 2
   // to 30 rows per lane x 1 to 7 waves per SIMD): it ends with those that try

@@ -54,7 +54,7 @@
 #include <limits.h>
 #include <math.h>
 
-#include "common.h"
+#include "device.h"
 
 namespace sdtw {
 namespace {
@@ -469,6 +469,7 @@ __global__ __launch_bounds__(64) void k_detect_events(const float* __restrict__ 
                                                       int32_t trim, int32_t keep, int32_t prefix,
                                                       float* __restrict__ out,
                                                       int32_t* __restrict__ counts) {
+  issue_first();
   __shared__ Scan::Shared sh;
   extern __shared__ int64_t ev_list[];  // [trim + keep]
   const int lane = (int)threadIdx.x;
@@ -557,6 +558,7 @@ __global__ __launch_bounds__(64) void k_events_continue(
     const float* __restrict__ raw, const int64_t* __restrict__ ranges,
     const int32_t* __restrict__ slots, EventState* __restrict__ states, int32_t trim,
     int32_t keep, float* __restrict__ out, int32_t* __restrict__ counts) {
+  issue_first();
   __shared__ Scan::Shared sh;
   extern __shared__ int64_t pend[];  // [keep + kPending]
   const int32_t r = (int32_t)blockIdx.x;

@@ -16,7 +16,7 @@
 
 #include <type_traits>
 
-#include "common.h"
+#include "device.h"
 
 namespace sdtw {
 namespace {
@@ -594,6 +594,7 @@ __global__ __launch_bounds__(64) void k_prep_queries(const float* __restrict__ r
                                                      float* __restrict__ z,
                                                      int16_t* __restrict__ codes,
                                                      int64_t* __restrict__ nsat) {
+  issue_first();
   __shared__ float buf[2 * kQChunk];
   const int32_t r = (int32_t)blockIdx.x;
   if (r >= nq) return;

@@ -58,6 +58,7 @@
 #include <algorithm>
 
 #include "cells.h"
+#include "device.h"
 
 namespace sdtw {
 namespace {
@@ -67,18 +68,20 @@ constexpr int kHaloWaves = 2;  // of a halo workgroup: the two recurrences of a 
 
 // LDS of a wave, in bytes: 128 groups of four reference values (the window
 // of the 64 steps of a block over 64 lanes), then four planes, one per step
-// modulo 4, each with a 16-byte slot per lane, a slot of zeros, a dump slot,
-// and per read of the wave 8 output slots and (STREAM) 8 slots of the
-// resident row.  Four workgroups of four waves fit on a CU.
+// modulo 4, each with a 16-byte slot per lane (the last, which no lane reads, is
+// the dump slot), a slot of zeros, and per read of the wave 8 output slots and
+// (STREAM) 8 slots of the resident row.  Four workgroups of four waves fit on a
+// CU, and one of STREAM beside three that are held apart (share_lds).
 template <bool STREAM>
 struct Lds {
   static constexpr int kReads = STREAM ? kRowsStreamReads : kRowsReads;
   static constexpr int kPairs = (kReads + 1) / 2;
   static constexpr int kY = 2048;  // bytes before the planes
-  static constexpr int kZero = 1024, kDump = 1040, kOut = 1056;
+  static constexpr int kZero = 1024, kDump = 16 * 63, kOut = 1040;
   static constexpr int kAcc = kOut + 128 * kReads;
   static constexpr int kPlane = kAcc + (STREAM ? 128 * kReads : 0);
   static constexpr int kBytes = kY + 4 * kPlane;
+  static_assert(kMainWaves * kBytes <= (128 - 3 * 33) * 1280);
 };
 
 __device__ __forceinline__ uint4 lds_get(const char* lds, uint32_t at) {
@@ -551,6 +554,11 @@ __device__ __forceinline__ void for_rows(int32_t rows, Fn&& f) {
 #undef SDTW_ROWS
 }
 
+// Waves on segments of up to this many columns (under 2 ms) issue before those of
+// long launches: 250 rows x 64 columns, 20 us alone, took 1.2 ms beside chunks on
+// 10 M columns, 0.07 ms so.
+constexpr int32_t kShortSegment = 16384;
+
 // (with few classes the arguments are read where they are)
 template <bool DPP>
 using Call = std::conditional_t<DPP, const RowsCall&, const RowsCall>;
@@ -564,6 +572,7 @@ __global__ __launch_bounds__(64 * kHaloWaves, 4) void k_rows_halo(RowsArgs a) {
   for (int k = 1; k < a.nclasses; ++k)
     if (at >= a.cls[k].first_halo) c = k;
   const RowClass cl = a.cls[c];
+  if (cl.segcols <= kShortSegment) issue_first();
   const int32_t in = at - cl.first_halo;
   const int32_t pack = cl.first_pack + in / (cl.nseg - 1), seg = 1 + in % (cl.nseg - 1);
   Call<DPP> call = a;
@@ -588,6 +597,7 @@ __global__ __launch_bounds__(64 * kMainWaves, 4) void k_rows_main(RowsArgs a) {
   for (int k = 1; k < a.nclasses; ++k)
     if (at >= a.cls[k].first_wave) c = k;
   const RowClass cl = a.cls[c];
+  if (cl.segcols <= kShortSegment) issue_first();
   const int32_t in = at - cl.first_wave;
   const int32_t pack = cl.first_pack + in / cl.nseg, seg = in % cl.nseg;
   Call<DPP> call = a;
@@ -651,13 +661,10 @@ __global__ __launch_bounds__(64 * kMainWaves, 4) void k_rows_main(RowsArgs a) {
   }
 }
 
-// LDS of a workgroup that leaves a CU no more than its even share of a
-// launch of `blocks` workgroups (`need` bytes each): the dispatcher would
-// otherwise fill some CUs and leave others empty.
-inline size_t even_lds(size_t need, int64_t blocks, int cus) {
-  const int64_t share = std::max<int64_t>((blocks + cus - 1) / std::max(cus, 1), 1);
-  const size_t want = (size_t)(160 * 1024 / share / 1280 * 1280);  // (allocated by 1,280 bytes)
-  return std::max(need, std::min<size_t>(want, (size_t)max_lds_bytes()));
+// The least LDS of a workgroup (which needs `need` bytes) that lets no more than
+// `share` of them onto a CU (160 KB, allocated by 1,280 bytes).
+inline size_t share_lds(size_t need, int64_t share) {
+  return std::max(need, (size_t)(128 / (share + 1) + 1) * 1280);
 }
 
 template <class F, bool STREAM, bool DPP>
@@ -669,9 +676,16 @@ hipError_t launch_t(const RowsArgs& a, hipStream_t st, int parts) {
   }
   if (!(parts & kRowsSweep)) return hipGetLastError();
   const int64_t blocks = (a.nwaves + kMainWaves - 1) / kMainWaves;
-  // (not where calls on other HIP streams have to find room on the same CUs)
+  // An even share of the workgroups for every CU (the dispatcher would fill some
+  // and leave others empty), and of chunk launches, which run for long beside short
+  // ones on other HIP streams, no more than leaves those a wave per SIMD and
+  // 37,120 bytes: 16 chunks of 400 rows x 59,796 columns beside 256 x 10 M columns
+  // waited 38 ms for a place when those took four waves per SIMD.
   const size_t need = kMainWaves * Lds<STREAM>::kBytes;
-  const size_t lds = STREAM ? need : even_lds(need, blocks, a.cus);
+  const int64_t even = std::max<int64_t>((blocks + a.cus - 1) / std::max(a.cus, 1), 1);
+  const int64_t most =
+      rows_side_by_side(STREAM, std::is_same_v<F, FmtF32>, a.cls[0].rows_per_lane);
+  const size_t lds = STREAM ? (even > most ? share_lds(need, most) : need) : need;
   hipError_t e = hipFuncSetAttribute((const void*)k_rows_main<F, STREAM, DPP>,
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;

@@ -24,7 +24,7 @@
 // plus 8 S in the second.
 #include <limits.h>
 
-#include "common.h"
+#include "device.h"
 
 namespace sdtw {
 namespace {
@@ -79,6 +79,7 @@ __device__ __forceinline__ uint64_t scan_min(const uint32_t* __restrict__ row, i
 __global__ __launch_bounds__(kThreads) void k_segment_min(const StreamItem* __restrict__ items,
                                                           int64_t n, int32_t S,
                                                           uint64_t* __restrict__ part) {
+  issue_first();
   __shared__ uint64_t sk[kThreads / 64];
   const int64_t blk = (int64_t)blockIdx.x;
   const int32_t s = (int32_t)(blk / S), seg = (int32_t)(blk % S);
@@ -94,6 +95,7 @@ __global__ __launch_bounds__(kThreads) void k_best_two(const StreamItem* __restr
                                                        const uint64_t* __restrict__ part,
                                                        void* best_cost, int32_t* best_end,
                                                        void* second_cost, int32_t* second_end) {
+  issue_first();
   __shared__ uint64_t sk[kThreads / 64];
   const int32_t s = (int32_t)blockIdx.x;
   const uint64_t* __restrict__ my = part + (int64_t)s * S;

@@ -44,7 +44,7 @@
 
 #include <mutex>
 
-#include "common.h"
+#include "device.h"
 
 namespace sdtw {
 
@@ -287,6 +287,7 @@ __global__ __launch_bounds__(kWideThreads, LowReg ? 3 : 1) void k_align_wide(
     int32_t m, uint64_t* __restrict__ flags, uint64_t* __restrict__ tile_key,
     uint32_t* __restrict__ ctrl, uint32_t* __restrict__ row, int row_in,
     const uint64_t* __restrict__ left_of_tile, const uint32_t* __restrict__ gate) {
+  issue_first();
   if (shut(gate)) return;
   constexpr int T = kWideThreads * C;
   __shared__ uint32_t sa[kWideThreads / 64], sd[kWideThreads / 64];
@@ -437,6 +438,7 @@ __global__ void k_wide_clear(WideClear c) { c.at((int64_t)blockIdx.x * blockDim.
 __global__ __launch_bounds__(1024) void k_wide_gate(const uint32_t* __restrict__ set, int32_t n,
                                                     int32_t limit, uint32_t* __restrict__ gate,
                                                     WideClear c) {
+  issue_first();
   __shared__ int32_t part[16];
   int32_t mine = 0;
   for (int32_t i = (int32_t)threadIdx.x; i < n; i += 1024) mine += (int32_t)set[i];
@@ -457,6 +459,7 @@ __global__ __launch_bounds__(kWideThreads) void k_wide_final(const uint64_t* __r
                                                              int32_t* cost, int32_t* end,
                                                              uint32_t* row_min,
                                                              const uint32_t* __restrict__ gate) {
+  issue_first();
   if (shut(gate)) return;
   __shared__ uint64_t sk[kWideThreads / 64];
   uint64_t k = ~0ull;
