@@ -254,7 +254,8 @@ int sdtw_free_reference(sdtw_ref ref);
  * the same read lengths.  Reads of up to 2,048 rows share waves that hold a
  * few rows of them per lane, and the reference is cut into column segments
  * that are aligned at once, as many as a cost model of the launch finds best
- * for the batch and the reference's length.  Longer reads, every read of
+ * for the batch and the reference's length.  Longer reads (and reads beside a
+ * few longer ones, whose launch would leave the device idle), every read of
  * a plan whose launch shape was set (sdtw_plan_set_config), and every read
  * against a reference of which so much lies in runs of 64 and more equal
  * values that by the model segments do not pay (from about a tenth on) run on

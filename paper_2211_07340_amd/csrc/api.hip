@@ -65,9 +65,10 @@ struct sdtw_plan_s {
   int32_t band_rows;              // target rows per band (0: as many bands as fit)
   int waves_per_cu;               // persistent grid density (bands x workgroups per CU)
   int cus;                        // compute units of the device
-  // Row-lane kernel (rows.h), for the reads of up to kRowsMaxM rows: order[nlong ..)
+  // Row-lane kernel (rows.h), for the reads of up to kRowsMaxM rows: order[nlong ..),
+  // or none (nlong == nq) beside few longer ones (split_pays)
   bool rows;                      // use it (a launch shape set by the caller: the skew kernel)
-  int32_t nlong;                  // reads too long for it
+  int32_t nlong;                  // reads that it does not take
   sdtw::RowLayout* lay[2];        // reads sharing waves; reads alone in theirs
   sdtw::RowPack* packs_dev[2];
   int64_t scratch_words;
@@ -623,11 +624,18 @@ int sdtw_plan_create(const int64_t* offsets_host, int32_t nq, int dtype, sdtw_pl
   if (p->cus <= 0) p->cus = 256;
   choose_config(p);
   p->rows = true;
-  while (p->nlong < nq && p->sorted_m[(size_t)p->nlong] > kRowsMaxM) ++p->nlong;
+  double long_rows = 0.0;
+  for (int32_t i = 0; i < nq; ++i) {
+    const int32_t m = p->sorted_m[(size_t)i];
+    (m > kRowsMaxM ? long_rows : p->short_rows) += m;
+    if (m > kRowsMaxM) ++p->nlong;
+  }
+  if (p->nlong && p->nlong < nq &&
+      !split_pays(max_m, p->sorted_m[(size_t)p->nlong], long_rows, p->short_rows, p->cus))
+    p->nlong = nq;
   std::vector<std::pair<int32_t, int32_t>> reads;
   for (int32_t i = p->nlong; i < nq; ++i)
     reads.emplace_back(order[(size_t)i], p->sorted_m[(size_t)i]);
-  for (const auto& rd : reads) p->short_rows += rd.second;
   for (int i = 0; i < 2; ++i) {
     if (i == 1 && !alone_pays(*p->lay[0], p->cus)) break;
     p->lay[i] = new (std::nothrow) RowLayout(rows_layout(reads, i == 1, kRowsReads));
@@ -1428,6 +1436,13 @@ int sdtw_stream_extend(const sdtw_stream* streams, int32_t ns, const void* chunk
   int32_t nskew = ns;
   if (!shaped)
     for (nskew = 0; nskew < ns && len(order[(size_t)nskew]) > kRowsMaxM;) ++nskew;
+  if (nskew > 0 && nskew < ns) {
+    double long_rows = 0.0, short_rows = 0.0;
+    for (int32_t t = 0; t < ns; ++t)
+      (t < nskew ? long_rows : short_rows) += (double)len(order[(size_t)t]);
+    const int32_t next = (int32_t)len(order[(size_t)nskew]);
+    if (!split_pays(max_m, next, long_rows, short_rows, cus)) nskew = ns;
+  }
   RowsArgs ra{};
   RowLayout lay;
   int64_t words = 0;

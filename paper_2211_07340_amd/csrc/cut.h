@@ -315,6 +315,20 @@ static int64_t rows_most_words(const RowLayout& lay, int cus) {
 static bool alone_pays(const RowLayout& shared, int cus) {
   return (int64_t)shared.packs.size() < 16 * (int64_t)cus;
 }
+// Whether reads of up to kRowsMaxM rows run on the row-lane kernel beside longer
+// ones, which run before them on the column-lane kernels: not if few long reads
+// leave more of the device idle meanwhile than the row-lane kernel saves on the
+// others.  In rows, all against the same columns: the device takes about 600
+// rows of a batch in the time of one of the longest read (21 ns a column and read
+// at 2 waves, 12.6e12 cells a second), and the row-lane kernel saves about 0.19 of
+// theirs (15.5e12).  One read of 4,096 rows and 2,000 of 500 x 59,796 columns: 16.1
+// ms apart, 12.1 together, tuned 10.1 and 7.2; 1,000 of 2,500 and 1,000 of 1,800:
+// 18.2 and 18.5.  (Reads of up to 64 rows have a launch of their own there too.)
+static bool split_pays(int32_t max_m, int32_t next_m, double long_rows, double short_rows,
+                       int cus) {
+  return next_m < skew_min_m(1) ||
+         600.0 / 256.0 * cus * max_m - long_rows < 0.19 * short_rows;
+}
 // The parts of the scratch of a cut launch.
 static void rows_scratch(RowsArgs& a, uint64_t* s) {
   if (!a.nhalo) return;

@@ -1,0 +1,91 @@
+"""Reads over 2,048 rows with shorter ones in a plan or a call: results as the
+oracle's, and a few long reads do not make the others wait for them, that is, the
+plan takes no longer than one whose launch shape, set to its own, keeps every
+read in one launch (a seventh more for the noise of one measurement; two launches
+in turn took a third more)."""
+import sys
+
+import numpy as np
+import pytest
+
+import oracle
+import synth
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+sd = pytest.importorskip("paper_2211_07340_amd")
+
+
+def fastest(call):
+    best = float("inf")
+    for _ in range(4):
+        torch.cuda.synchronize()
+        e0, e1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        e0.record()
+        out = call()
+        e1.record()
+        torch.cuda.synchronize()
+        best = min(best, e0.elapsed_time(e1))
+    return best, out
+
+
+def test_few_long_reads():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    dev = torch.device("cuda:0")
+    rng = np.random.default_rng(8)
+    ref_np = rng.integers(-3000, 3000, 59_796).astype(np.int16)
+    ref = sd.Reference(torch.from_numpy(ref_np).to(dev))
+    for lens in ([4096] + [500] * 2000, [4096] * 64 + [1500] * 1000):
+        q, offs = synth.csr([rng.integers(-3000, 3000, m).astype(np.int16) for m in lens])
+        qd = torch.from_numpy(q).to(dev)
+        plan, shaped = sd.Plan(offs, sd.I16), sd.Plan(offs, sd.I16)
+        c = shaped.config
+        shaped.set_config(c["strip"], c["chains"], c["waves_per_cu"], c["bands"])
+        want, _ = fastest(lambda: sd.align_batch(ref, shaped, qd))
+        got, (cost, end) = fastest(lambda: sd.align_batch(ref, plan, qd))
+        print(f"{lens.count(4096)} reads of 4,096 rows with {lens.count(lens[-1])} of "
+              f"{lens[-1]}: {got:.2f} ms, {want:.2f} in one launch", flush=True)
+        sys.stdout.flush()
+        for i in (0, len(lens) - 1):
+            assert (int(cost[i].item()), int(end[i].item())) == \
+                oracle.sdtw_i64(q[offs[i]:offs[i + 1]], ref_np)
+        plan.close()
+        shaped.close()
+        assert got < 8 / 7 * want
+    ref.close()
+
+
+@pytest.mark.parametrize("dt", ["i16", "f32"])
+@pytest.mark.parametrize("lens", [[2049, 5], [2049] + [2048] * 300, [3000] * 40 + [30] * 40,
+                                  [2100] * 8 + [700] * 900])
+def test_either_way_equals_the_oracle(lens, dt):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    dev = torch.device("cuda:0")
+    rng = np.random.default_rng(len(lens))
+
+    def values(n):
+        v = rng.integers(-3000, 3000, n)
+        return v.astype(np.int16) if dt == "i16" else (v / 64).astype(np.float32)
+
+    ref_np = values(3001)
+    q, offs = synth.csr([values(m) for m in lens])
+    q = q.astype(ref_np.dtype)
+    kind, code = (oracle.I64, sd.I16) if dt == "i16" else (oracle.F32, sd.F32)
+    wc, we, _ = oracle.batch(kind, q, offs, ref_np)
+    ref = sd.Reference(torch.from_numpy(ref_np).to(dev))
+    plan = sd.Plan(offs, code)
+    qd = torch.from_numpy(q).to(dev)
+    print(f"{len(lens)} reads of {lens[0]} and {lens[-1]} rows {dt}", flush=True)
+    sys.stdout.flush()
+    streams = [sd.Stream(ref) for _ in lens]
+    for cost, end in (sd.align_batch(ref, plan, qd), sd.stream_extend(streams, qd, offs)):
+        torch.cuda.synchronize()
+        assert np.array_equal(cost.cpu().numpy().astype(np.float64), wc)
+        assert np.array_equal(end.cpu().numpy(), we)
+    for s in streams:
+        s.close()
+    plan.close()
+    ref.close()
