@@ -59,7 +59,7 @@ enum sdtw_dtype {
 enum sdtw_status {
   SDTW_OK = 0,
   SDTW_EINVAL = 1,  /* bad argument (null pointer, size, dtype, ...)      */
-  SDTW_ENOMEM = 2,  /* device allocation failed                           */
+  SDTW_ENOMEM = 2,  /* device or host allocation failed                   */
   SDTW_EBUDGET = 3, /* resident-row pool budget exhausted                 */
   SDTW_EDEVICE = 4, /* HIP runtime / kernel error                         */
   SDTW_ESTATE = 5   /* object in the wrong state (closed, still in use)   */

@@ -301,6 +301,13 @@ using namespace sdtw;
     if (!(cond)) return set_error(SDTW_EINVAL, __VA_ARGS__); \
   } while (0)
 
+// The end of an entry point whose body allocates on the host: nothing is thrown
+// through the C ABI.
+#define SDTW_NO_MEMORY(who)                                      \
+  catch (const std::bad_alloc&) {                                \
+    return set_error(SDTW_ENOMEM, "%s: host allocation", who);   \
+  }
+
 extern "C" {
 
 const char* sdtw_last_error(void) { return g_err; }
@@ -592,7 +599,7 @@ static hipError_t plan_free(sdtw_plan_s* p) {
   return first;
 }
 
-int sdtw_plan_create(const int64_t* offsets_host, int32_t nq, int dtype, sdtw_plan* out) {
+int sdtw_plan_create(const int64_t* offsets_host, int32_t nq, int dtype, sdtw_plan* out) try {
   SDTW_REQUIRE(offsets_host && out, "sdtw_plan_create: null pointer");
   SDTW_REQUIRE(nq >= 1, "sdtw_plan_create: nq=%d < 1", nq);
   SDTW_REQUIRE(dtype == SDTW_F32 || dtype == SDTW_I16, "sdtw_plan_create: bad dtype %d", dtype);
@@ -612,8 +619,11 @@ int sdtw_plan_create(const int64_t* offsets_host, int32_t nq, int dtype, sdtw_pl
     return len(a) != len(b) ? len(a) > len(b) : a < b;
   });
 
-  sdtw_plan_s* p = new (std::nothrow) sdtw_plan_s();
-  if (!p) return set_error(SDTW_ENOMEM, "sdtw_plan_create: host allocation");
+  struct Free {
+    void operator()(sdtw_plan_s* plan) const { (void)plan_free(plan); }
+  };
+  std::unique_ptr<sdtw_plan_s, Free> own(new sdtw_plan_s());
+  sdtw_plan_s* const p = own.get();
   p->device = current_device();
   p->dtype = dtype;
   p->nq = nq;
@@ -638,12 +648,7 @@ int sdtw_plan_create(const int64_t* offsets_host, int32_t nq, int dtype, sdtw_pl
     reads.emplace_back(order[(size_t)i], p->sorted_m[(size_t)i]);
   for (int i = 0; i < 2; ++i) {
     if (i == 1 && !alone_pays(*p->lay[0], p->cus)) break;
-    p->lay[i] = new (std::nothrow) RowLayout(rows_layout(reads, i == 1, kRowsReads));
-    if (!p->lay[i]) {
-      delete p->lay[0];
-      delete p;
-      return set_error(SDTW_ENOMEM, "sdtw_plan_create: host allocation");
-    }
+    p->lay[i] = new RowLayout(rows_layout(reads, i == 1, kRowsReads));
     p->scratch_words = std::max(p->scratch_words, rows_most_words(*p->lay[i], p->cus));
   }
   int rc = check_hip(hipMalloc((void**)&p->offs_dev, sizeof(int64_t) * (size_t)(nq + 1)),
@@ -669,13 +674,10 @@ int sdtw_plan_create(const int64_t* offsets_host, int32_t nq, int dtype, sdtw_pl
     p->scratch = nullptr;
     p->scratch_words = 0;  // one segment per pack
   }
-  if (rc) {
-    (void)plan_free(p);
-    return rc;
-  }
-  *out = p;
+  if (rc) return rc;
+  *out = own.release();
   return SDTW_OK;
-}
+} SDTW_NO_MEMORY("sdtw_plan_create")
 
 int sdtw_plan_info(sdtw_plan plan, int32_t* nq, int* dtype, int32_t* max_m) {
   SDTW_REQUIRE(plan, "sdtw_plan_info: null plan");
@@ -751,7 +753,7 @@ static int align_batch_impl(sdtw_ref ref, sdtw_plan plan, const void* q_dev, voi
                             int32_t* end_dev, hipStream_t st, int64_t n);
 
 int sdtw_align_batch(sdtw_ref ref, sdtw_plan plan, const void* q_dev, void* cost_dev,
-                     int32_t* end_dev, void* stream) {
+                     int32_t* end_dev, void* stream) try {
   SDTW_REQUIRE(ref && plan, "sdtw_align_batch: null reference or plan");
   SDTW_REQUIRE(q_dev && cost_dev && end_dev, "sdtw_align_batch: null device pointer");
   SDTW_REQUIRE(ref->dtype == plan->dtype, "sdtw_align_batch: reference dtype %d != plan dtype %d",
@@ -760,7 +762,7 @@ int sdtw_align_batch(sdtw_ref ref, sdtw_plan plan, const void* q_dev, void* cost
                ref->device, plan->device);
   if (int rc = require_device(ref->device, "sdtw_align_batch")) return rc;
   return align_batch_impl(ref, plan, q_dev, cost_dev, end_dev, (hipStream_t)stream, ref->n);
-}
+} SDTW_NO_MEMORY("sdtw_align_batch")
 
 // Cuts the plan's reads of up to kRowsMaxM rows for n columns of ref; false if
 // they are better off on the column-lane kernels there.
@@ -936,7 +938,7 @@ static hipError_t launch_one(sdtw_ref ref, OneRead& o, uint64_t* scratch, hipStr
 }
 
 int sdtw_align_one_wide(sdtw_ref ref, const void* q_dev, int32_t M, int cols, void* cost_dev,
-                        int32_t* end_dev, void* stream) {
+                        int32_t* end_dev, void* stream) try {
   SDTW_REQUIRE(ref, "sdtw_align_one_wide: null reference");
   SDTW_REQUIRE(q_dev && cost_dev && end_dev, "sdtw_align_one_wide: null device pointer");
   SDTW_REQUIRE(ref->dtype == SDTW_I16, "sdtw_align_one_wide: int16 references only");
@@ -975,7 +977,7 @@ int sdtw_align_one_wide(sdtw_ref ref, const void* q_dev, int32_t M, int cols, vo
   const int rc_ev = check_hip(hipEventRecord(tok->ev, st), "sdtw_align_one_wide: record");
   if (!rc_ev) sl.last = tok;
   return rc ? rc : rc_ev;
-}
+} SDTW_NO_MEMORY("sdtw_align_one_wide")
 
 int sdtw_align_one_wide_noalloc(sdtw_ref ref, const void* q_dev, int32_t M, int cols,
                                 void* cost_dev, int32_t* end_dev, void* stream) {
@@ -1114,7 +1116,7 @@ void tune_file_write_locked() {
 extern "C" {
 
 int sdtw_plan_autotune(sdtw_ref ref, sdtw_plan plan, const void* q_dev, void* cost_dev,
-                       int32_t* end_dev, int64_t max_columns, void* stream) {
+                       int32_t* end_dev, int64_t max_columns, void* stream) try {
   SDTW_REQUIRE(ref && plan, "sdtw_plan_autotune: null reference or plan");
   SDTW_REQUIRE(q_dev && cost_dev && end_dev, "sdtw_plan_autotune: null device pointer");
   SDTW_REQUIRE(ref->dtype == plan->dtype,
@@ -1157,6 +1159,7 @@ int sdtw_plan_autotune(sdtw_ref ref, sdtw_plan plan, const void* q_dev, void* co
             cand.push_back({strip, chains, bands, w / 2, target});
         }
       }
+  std::vector<float> cand_ms(cand.size(), 0.f);
   hipEvent_t e0 = nullptr, e1 = nullptr;
   if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) {
     if (e0) (void)hipEventDestroy(e0);
@@ -1172,7 +1175,6 @@ int sdtw_plan_autotune(sdtw_ref ref, sdtw_plan plan, const void* q_dev, void* co
   // cold device run slower), a single timing can misorder shapes a few
   // percent apart, and a clock that drifts during the passes favours no
   // position in the list
-  std::vector<float> cand_ms(cand.size(), 0.f);
   for (int pass = 0; pass < 2 && !rc; ++pass) {
     for (size_t j = 0; j < cand.size(); ++j) {
       const size_t i = pass == 0 ? j : cand.size() - 1 - j;
@@ -1218,9 +1220,9 @@ int sdtw_plan_autotune(sdtw_ref ref, sdtw_plan plan, const void* q_dev, void* co
     return SDTW_OK;
   tune_file_write_locked();
   return SDTW_OK;
-}
+} SDTW_NO_MEMORY("sdtw_plan_autotune")
 
-int sdtw_plan_use_tuned(sdtw_ref ref, sdtw_plan plan, int* found) {
+int sdtw_plan_use_tuned(sdtw_ref ref, sdtw_plan plan, int* found) try {
   SDTW_REQUIRE(ref && plan, "sdtw_plan_use_tuned: null reference or plan");
   const TuneKey key = tune_key(plan, ref->n);
   std::lock_guard<std::mutex> g(g_tune_mu);
@@ -1236,7 +1238,7 @@ int sdtw_plan_use_tuned(sdtw_ref ref, sdtw_plan plan, int* found) {
     plan->rows = true;
   }
   return SDTW_OK;
-}
+} SDTW_NO_MEMORY("sdtw_plan_use_tuned")
 
 // ---------------------------------------------------------------------------
 // streaming extension
@@ -1278,7 +1280,7 @@ int sdtw_row_budget_info(int64_t* budget, int64_t* in_use, int64_t* cached) {
   return SDTW_OK;
 }
 
-int sdtw_stream_open(sdtw_ref ref, sdtw_stream* out) {
+int sdtw_stream_open(sdtw_ref ref, sdtw_stream* out) try {
   SDTW_REQUIRE(ref && out, "sdtw_stream_open: null pointer");
   if (int rc = require_device(ref->device, "sdtw_stream_open")) return rc;
   RowPool* pl = pool_for(ref->device);
@@ -1328,7 +1330,7 @@ int sdtw_stream_open(sdtw_ref ref, sdtw_stream* out) {
   ref->open_streams++;
   *out = s;
   return SDTW_OK;
-}
+} SDTW_NO_MEMORY("sdtw_stream_open")
 
 int sdtw_stream_info(sdtw_stream s, int32_t* rows, int64_t* n) {
   SDTW_REQUIRE(s, "sdtw_stream_info: null stream");
@@ -1337,7 +1339,7 @@ int sdtw_stream_info(sdtw_stream s, int32_t* rows, int64_t* n) {
   return SDTW_OK;
 }
 
-int sdtw_stream_close(sdtw_stream s) {
+int sdtw_stream_close(sdtw_stream s) try {
   SDTW_REQUIRE(s, "sdtw_stream_close: null stream");
   // the row may still be read or written by enqueued work
   if (s->last && s->last->ev) {
@@ -1354,7 +1356,7 @@ int sdtw_stream_close(sdtw_stream s) {
   s->ref->open_streams--;
   delete s;
   return SDTW_OK;
-}
+} SDTW_NO_MEMORY("sdtw_stream_close")
 
 int sdtw_stream_copy_row(sdtw_stream s, void* dst_dev, void* stream) {
   SDTW_REQUIRE(s && dst_dev, "sdtw_stream_copy_row: null pointer");
@@ -1383,7 +1385,7 @@ int sdtw_stream_set_config(sdtw_ref ref, int strip, int bands) {
 
 int sdtw_stream_extend(const sdtw_stream* streams, int32_t ns, const void* chunk_dev,
                        const int64_t* chunk_offsets_host, void* cost_dev, int32_t* end_dev,
-                       void* stream) {
+                       void* stream) try {
   SDTW_REQUIRE(streams && chunk_dev && chunk_offsets_host && cost_dev && end_dev,
                "sdtw_stream_extend: null pointer");
   SDTW_REQUIRE(ns >= 1, "sdtw_stream_extend: ns=%d < 1", ns);
@@ -1597,10 +1599,10 @@ int sdtw_stream_extend(const sdtw_stream* streams, int32_t ns, const void* chunk
     streams[i]->last = tok;
   }
   return SDTW_OK;
-}
+} SDTW_NO_MEMORY("sdtw_stream_extend")
 
 int sdtw_stream_extend_wide(sdtw_stream s, const void* chunk_dev, int32_t M, int cols,
-                            void* cost_dev, int32_t* end_dev, void* stream) {
+                            void* cost_dev, int32_t* end_dev, void* stream) try {
   SDTW_REQUIRE(s && chunk_dev && cost_dev && end_dev, "sdtw_stream_extend_wide: null pointer");
   const sdtw_ref ref = s->ref;
   SDTW_REQUIRE(ref->dtype == SDTW_I16, "sdtw_stream_extend_wide: int16 references only");
@@ -1646,11 +1648,11 @@ int sdtw_stream_extend_wide(sdtw_stream s, const void* chunk_dev, int32_t M, int
   s->rows += M;
   s->last = tok;
   return SDTW_OK;
-}
+} SDTW_NO_MEMORY("sdtw_stream_extend_wide")
 
 int sdtw_stream_best_two(const sdtw_stream* streams, int32_t ns, int32_t window,
                          void* best_cost_dev, int32_t* best_end_dev, void* second_cost_dev,
-                         int32_t* second_end_dev, void* stream) {
+                         int32_t* second_end_dev, void* stream) try {
   SDTW_REQUIRE(streams && best_cost_dev && best_end_dev && second_cost_dev && second_end_dev,
                "sdtw_stream_best_two: null pointer");
   SDTW_REQUIRE(ns >= 1, "sdtw_stream_best_two: ns=%d < 1", ns);
@@ -1701,7 +1703,7 @@ int sdtw_stream_best_two(const sdtw_stream* streams, int32_t ns, int32_t window,
   if (rc) return rc;
   for (int32_t i = 0; i < ns; ++i) streams[i]->last = tok;  // close waits for the read
   return SDTW_OK;
-}
+} SDTW_NO_MEMORY("sdtw_stream_best_two")
 
 }  // extern "C"
 
