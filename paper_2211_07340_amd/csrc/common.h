@@ -257,9 +257,9 @@ hipError_t launch_rows_f32_stream(const RowsArgs& a, hipStream_t st, int parts);
 // Workgroups of a launch that run side by side on a CU (waves on a SIMD): four, and
 // of chunk launches fewer, so that calls on other HIP streams find room.  256 and
 // 1,024 chunks of 400 and 100 rows x 9,999,990 columns on int16: 63.9 and 82.7 ms
-// with four, 65.9 and 87.5 with three; on float32, whose cells like two or four
-// better than three, 62.6 and 63.6 with four and two (20 rows per lane), and below
-// 12 rows per lane three.
+// with four, 65.7 and 86.8 with three; on float32, whose cells like two or four
+// better than three, 62.6 and 60.8 with four and two (20 rows per lane), and 90.2 and
+// 90.3 with four and three (6).
 constexpr int rows_side_by_side(bool stream, bool f32, int32_t rows_per_lane) {
   return stream ? (f32 && rows_per_lane >= 12 ? 2 : 3) : 4;
 }

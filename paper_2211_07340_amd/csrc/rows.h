@@ -676,16 +676,20 @@ hipError_t launch_t(const RowsArgs& a, hipStream_t st, int parts) {
   }
   if (!(parts & kRowsSweep)) return hipGetLastError();
   const int64_t blocks = (a.nwaves + kMainWaves - 1) / kMainWaves;
-  // An even share of the workgroups for every CU (the dispatcher would fill some
-  // and leave others empty), and of chunk launches, which run for long beside short
-  // ones on other HIP streams, no more than leaves those a wave per SIMD and
-  // 37,120 bytes: 16 chunks of 400 rows x 59,796 columns beside 256 x 10 M columns
-  // waited 38 ms for a place when those took four waves per SIMD.
+  // Long launches: an even share of the workgroups for every CU (the dispatcher
+  // would fill some and leave others empty: 64 chunks of 400 rows x 10 M columns 18.0
+  // ms with three on each, 18.6 as they come), and of chunk launches no more than
+  // leaves short calls on other HIP streams a wave per SIMD and 37,120 bytes: 16
+  // chunks x 59,796 columns beside 256 x 10 M columns waited 38 ms for a place when
+  // those took four waves per SIMD.  Short launches reserve nothing, to find room
+  // there (at 0.5% of one read's and 0.8% of 48 reads' time alone).
   const size_t need = kMainWaves * Lds<STREAM>::kBytes;
   const int64_t even = std::max<int64_t>((blocks + a.cus - 1) / std::max(a.cus, 1), 1);
   const int64_t most =
       rows_side_by_side(STREAM, std::is_same_v<F, FmtF32>, a.cls[0].rows_per_lane);
-  const size_t lds = STREAM ? (even > most ? share_lds(need, most) : need) : need;
+  int32_t longest = 0;
+  for (int k = 0; k < a.nclasses; ++k) longest = std::max(longest, a.cls[k].segcols);
+  const size_t lds = longest <= kShortSegment ? need : share_lds(need, std::min(even, most));
   hipError_t e = hipFuncSetAttribute((const void*)k_rows_main<F, STREAM, DPP>,
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
