@@ -394,7 +394,7 @@ int sdtw_align_one(sdtw_ref ref, const void* q_dev, int32_t M, void* cost_dev,
  *          most 64 tiles, else into at most 256, else 32: the fastest choice
  *          measured for each reference length).
  *   cost_dev  out int32[1]; end_dev out int32[1] (0-based column).
- * Enqueues two to five kernels and records an event that tracks the reuse of
+ * Enqueues one to five kernels and records an event that tracks the reuse of
  * its library-owned scratch (64 MiB per call in flight unless more is needed:
  * 8 bytes per tile per row for the row scan, 4 bytes per row and segment), so
  * the call is not for graph capture.  If a
@@ -509,10 +509,10 @@ int sdtw_stream_extend(const sdtw_stream* streams, int32_t ns, const void* chunk
  * Extend one stream by one chunk over the whole device (section 2.2's
  * per-chunk decision, Eq. 1 continued from the resident row), as
  * sdtw_align_one_wide does a whole read, starting from the stream's
- * resident row and writing the new last row back over it.  For a few
- * chunks against a long reference, whose batched extension is bounded by
- * one chunk's four waves, this answers in milliseconds; it uses the whole
- * device per chunk, so batches of many chunks belong to sdtw_stream_extend.
+ * resident row and writing the new last row back over it.  It uses the whole
+ * device for the chunk, so batches of chunks belong to sdtw_stream_extend,
+ * which spreads them over the device at once (400 rows x 10 M columns: 0.55 ms
+ * for one chunk, 5.9 ms for 16 in one batch).
  * The two may extend the same stream in turn (one resident row format).
  *   chunk_dev  M int16 values (device); the stream's rows plus M must stay
  *              <= SDTW_MAX_QUERY (EINVAL otherwise; sdtw_stream_extend

@@ -879,7 +879,9 @@ struct OneRead {
   int64_t words = 0;  // scratch of the row-lane kernel (the row scan's follows)
 };
 constexpr int64_t kScanBehind = int64_t(1) << 20;  // columns
-constexpr int32_t kMostUnsettled = 16;             // segments left to their neighbours
+// Segments left to their neighbours: a wave that walks 16 of 250 rows x 9,999,990
+// columns takes as long as the row scan, 2.5 and 2.1 ms.
+constexpr int32_t kMostUnsettled = 16;
 
 static int64_t one_words(const OneRead& o, int64_t n, int32_t m) {
   return o.words + (o.cols ? wide_scratch_words(n, m, o.cols) : 0) + 1;

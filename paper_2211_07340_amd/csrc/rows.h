@@ -7,9 +7,9 @@
 // the row above its own from the lane to its left (through LDS, written a
 // step earlier) and the four reference values from LDS.  There is no tile to
 // switch and no row to hand from tile to tile, so a step is almost nothing
-// but cells: 8 R VALU instructions (v_min3_u32 + v_sad_u32, or on float32
-// v_sub + v_min3 + v_add, 8 cycles per 64 cells either way) and about one
-// more.  Reads of 64 R rows or fewer share a wave, each on its own lanes.
+// but cells: 8 R VALU instructions on int16 (v_min3_u32 + v_sad_u32) and 12 R on
+// float32 (v_sub + v_min3 + v_add; 8 cycles per 64 cells either way) and about
+// one more.  Reads of 64 R rows or fewer share a wave, each on its own lanes.
 //
 // Uneven rows.  A read of M rows takes L lanes, the first a = M - L (R - 1)
 // of them with R rows and the others with R - 1, which leaves no row of the
@@ -43,15 +43,15 @@
 //
 // What bounds it, and what it measured (MI355X, against the column-lane
 // kernels of align.hip and the row scan of wide.hip that ran before).  The
-// sweep is bound by VALU issue: 2.02 to 2.05 instructions per 64 cells from 16
-// rows per lane up, of which 2 are the cells', at 4.3 to 4.5 cycles each with
-// three or four waves on a SIMD (int16; bare v_min3_u32 and v_sad_u32 reach
-// 4.5), the rest being clock (2.2-2.35 of the 2.4 GHz, 2.0 on float32) and idle
+// sweep is bound by VALU issue: on int16 2.02 to 2.05 instructions per 64 cells from
+// 16 rows per lane up, of which 2 are the cells' (float32: 3.02 and 3), at 4.3 to
+// 4.5 cycles each with three or four waves on a SIMD (bare v_min3_u32 and v_sad_u32
+// reach 4.5), the rest being clock (2.2-2.35 of the 2.4 GHz, 2.0 on float32) and idle
 // lanes.  1,024 reads of 250-500 rows x 9,999,990 columns 306 -> 224 ms, 4,096 of
-// 250 x 59,796 in float32 4.2 -> 3.4 ms, 8,192 of 100-2,000 x 59,796 34.3 -> 32.5
+// 250 x 59,796 in float32 4.2 -> 3.4 ms, 8,192 of 100-2,000 x 59,796 34.3 -> 32.4
 // ms, 48 of 20-300 x 59,796 2.88 -> 0.14 ms, one of 250 x 9,999,990 2.09 -> 0.29 ms
 // and x 59,796 0.53 -> 0.06 ms, two 400-row chunks on 256 resident rows x 9,999,990
-// 340 -> 127 ms, on 4 one by one 26.8 -> 4.4 ms.
+// 340 -> 129 ms, on 4 one by one 26.8 -> 4.3 ms.
 #pragma once
 #include <limits.h>
 
@@ -437,7 +437,8 @@ __device__ __forceinline__ void halo_body(const RowsCall& a, const RowClass& cl,
   H = (H + 3) & ~3;
   uint32_t* const sw = (uint32_t*)smem;  // the exchange: (R + 1) words per lane
   bool ok = false;
-  // (three times, and for a chunk on a reference without runs of equal values as
+  // (three times: reads that repeat the reference to the value settle within
+  // 1.6 M, at the second; and for a chunk on a reference without runs of equal values as
   // long as the halo is shorter than the segment that the wave to the left would
   // walk instead; where such runs are, tries in vain would take 16 chunks of 400 on
   // 9,999,990 columns, a fiftieth of them equal, from 24 to 40 ms)

@@ -44,17 +44,16 @@ This module simulates the channels and runs the decisions through the C ABI:
 ``mode="recompute"`` aligns every chunk's whole prefix from scratch instead
 (a fresh stream extended by the full prefix), for comparison.
 
-Few chunks against a long reference.  A batched extension's time is that of
-one chunk on its few waves (about 0.18 s for 400 events against 10 M
-columns) however few chunks it holds, while sdtw_stream_extend_wide extends
-one chunk over the whole device in a few milliseconds.  A batch of at most
+Few chunks against a long reference.  A batched extension spreads its chunks
+over the device (5.9 ms for 16 of 400 events against 10 M columns), and
+sdtw_stream_extend_wide one chunk (0.55 ms).  A batch of at most
 ``wide_chunks`` chunks (per target, by default the number whose whole-device
 calls take no longer than one batched launch, measured at calibration) is
 extended chunk by chunk over the whole device (``wide_chunks`` in the
 report counts them); ``wide_burst_ms`` caps such a batch's duration, since
 the whole device is its meanwhile and other targets' batches wait.  With
 ``wide_streams=2`` the chunks alternate between two HIP streams (one
-chunk's look-back waits overlap the other's rows), which pays only where
+chunk's launches start as the other's end), which pays only where
 the second stream has a hardware queue of its own: one shared with the
 target's other stream serialises the two.
 
@@ -296,7 +295,7 @@ class ReadUntilServer:
             t.streams = _server_streams(torch, i * k, k)
         # one more per target: whole-device extensions of a batch alternate
         # between the batch's stream and this one, so that one chunk's
-        # look-back waits overlap another chunk's rows
+        # launches start as another's end
         for i, t in enumerate(self.targets):
             t.wide_aux = _server_streams(torch, len(self.targets) * k + i, 1)[0]
         if self.cfg.row_budget_bytes is not None:
