@@ -254,6 +254,16 @@ hipError_t launch_rows_i16(const RowsArgs& a, hipStream_t st, int parts);
 hipError_t launch_rows_f32(const RowsArgs& a, hipStream_t st, int parts);
 hipError_t launch_rows_i16_stream(const RowsArgs& a, hipStream_t st, int parts);
 hipError_t launch_rows_f32_stream(const RowsArgs& a, hipStream_t st, int parts);
+// Waves on segments of up to this many columns (under 2 ms) issue before those of
+// long launches: 250 rows x 64 columns, 20 us alone, took 1.2 ms beside chunks on
+// 10 M columns, 0.07 ms so.  A launch of such waves alone is a short one.
+constexpr int32_t kShortSegment = 16384;
+inline bool rows_short(const RowsArgs& a) {
+  int32_t longest = 0;
+  for (int k = 0; k < a.nclasses; ++k)
+    if (a.cls[k].segcols > longest) longest = a.cls[k].segcols;
+  return longest <= kShortSegment;
+}
 // Workgroups of a launch that run side by side on a CU (waves on a SIMD): four, and
 // of chunk launches fewer, so that calls on other HIP streams find room.  256 and
 // 1,024 chunks of 400 and 100 rows x 9,999,990 columns on int16: 63.9 and 82.7 ms

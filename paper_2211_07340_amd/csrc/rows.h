@@ -68,16 +68,18 @@ constexpr int kHaloWaves = 2;  // of a halo workgroup: the two recurrences of a 
 
 // LDS of a wave, in bytes: 128 groups of four reference values (the window
 // of the 64 steps of a block over 64 lanes), then four planes, one per step
-// modulo 4, each with a 16-byte slot per lane (the last, which no lane reads, is
-// the dump slot), a slot of zeros, and per read of the wave 8 output slots and
+// modulo 4, each with a 16-byte slot per lane, a slot of zeros, a dump slot (STREAM:
+// the last lane's, which none reads), and per read of the wave 8 output slots and
 // (STREAM) 8 slots of the resident row.  Four workgroups of four waves fit on a
-// CU, and one of STREAM beside three that are held apart (share_lds).
+// CU, and one of either kind beside three of STREAM that are held apart
+// (share_lds).
 template <bool STREAM>
 struct Lds {
   static constexpr int kReads = STREAM ? kRowsStreamReads : kRowsReads;
   static constexpr int kPairs = (kReads + 1) / 2;
   static constexpr int kY = 2048;  // bytes before the planes
-  static constexpr int kZero = 1024, kDump = 16 * 63, kOut = 1040;
+  static constexpr int kZero = 1024, kDump = STREAM ? 16 * 63 : 1040;
+  static constexpr int kOut = STREAM ? 1040 : 1056;
   static constexpr int kAcc = kOut + 128 * kReads;
   static constexpr int kPlane = kAcc + (STREAM ? 128 * kReads : 0);
   static constexpr int kBytes = kY + 4 * kPlane;
@@ -555,11 +557,6 @@ __device__ __forceinline__ void for_rows(int32_t rows, Fn&& f) {
 #undef SDTW_ROWS
 }
 
-// Waves on segments of up to this many columns (under 2 ms) issue before those of
-// long launches: 250 rows x 64 columns, 20 us alone, took 1.2 ms beside chunks on
-// 10 M columns, 0.07 ms so.
-constexpr int32_t kShortSegment = 16384;
-
 // (with few classes the arguments are read where they are)
 template <bool DPP>
 using Call = std::conditional_t<DPP, const RowsCall&, const RowsCall>;
@@ -573,7 +570,7 @@ __global__ __launch_bounds__(64 * kHaloWaves, 4) void k_rows_halo(RowsArgs a) {
   for (int k = 1; k < a.nclasses; ++k)
     if (at >= a.cls[k].first_halo) c = k;
   const RowClass cl = a.cls[c];
-  if (cl.segcols <= kShortSegment) issue_first();
+  issue_first_if_short(cl.segcols);
   const int32_t in = at - cl.first_halo;
   const int32_t pack = cl.first_pack + in / (cl.nseg - 1), seg = 1 + in % (cl.nseg - 1);
   Call<DPP> call = a;
@@ -598,7 +595,7 @@ __global__ __launch_bounds__(64 * kMainWaves, 4) void k_rows_main(RowsArgs a) {
   for (int k = 1; k < a.nclasses; ++k)
     if (at >= a.cls[k].first_wave) c = k;
   const RowClass cl = a.cls[c];
-  if (cl.segcols <= kShortSegment) issue_first();
+  issue_first_if_short(cl.segcols);
   const int32_t in = at - cl.first_wave;
   const int32_t pack = cl.first_pack + in / cl.nseg, seg = in % cl.nseg;
   Call<DPP> call = a;
@@ -683,14 +680,12 @@ hipError_t launch_t(const RowsArgs& a, hipStream_t st, int parts) {
   // leaves short calls on other HIP streams a wave per SIMD and 37,120 bytes: 16
   // chunks x 59,796 columns beside 256 x 10 M columns waited 38 ms for a place when
   // those took four waves per SIMD.  Short launches reserve nothing, to find room
-  // there (at 0.5% of one read's and 0.8% of 48 reads' time alone).
+  // there; alone they take the same time either way.
   const size_t need = kMainWaves * Lds<STREAM>::kBytes;
   const int64_t even = std::max<int64_t>((blocks + a.cus - 1) / std::max(a.cus, 1), 1);
   const int64_t most =
       rows_side_by_side(STREAM, std::is_same_v<F, FmtF32>, a.cls[0].rows_per_lane);
-  int32_t longest = 0;
-  for (int k = 0; k < a.nclasses; ++k) longest = std::max(longest, a.cls[k].segcols);
-  const size_t lds = longest <= kShortSegment ? need : share_lds(need, std::min(even, most));
+  const size_t lds = rows_short(a) ? need : share_lds(need, std::min(even, most));
   hipError_t e = hipFuncSetAttribute((const void*)k_rows_main<F, STREAM, DPP>,
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
