@@ -270,7 +270,7 @@ int sdtw_free_reference(sdtw_ref ref);
  *   dtype         SDTW_F32 or SDTW_I16 (the query dtype of later calls).
  *   out           receives the plan (device memory is allocated here: the
  *                 layout, at most 150 bytes per read, and the segments' scratch,
- *                 5 to 35 MB for a few reads and never more than 101 MB; where
+ *                 up to 40 MB for a few reads and never more than 101 MB; where
  *                 that cannot be had the reference is not cut).
  */
 int sdtw_plan_create(const int64_t* offsets_host, int32_t nq, int dtype,
