@@ -17,17 +17,14 @@ torch = pytest.importorskip("torch")
 sd = pytest.importorskip("paper_2211_07340_amd")
 
 
-def fastest(call):
-    best = float("inf")
-    for _ in range(4):
-        torch.cuda.synchronize()
-        e0, e1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
-        e0.record()
-        out = call()
-        e1.record()
-        torch.cuda.synchronize()
-        best = min(best, e0.elapsed_time(e1))
-    return best, out
+def timed(call):
+    torch.cuda.synchronize()
+    e0, e1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+    e0.record()
+    out = call()
+    e1.record()
+    torch.cuda.synchronize()
+    return e0.elapsed_time(e1), out
 
 
 def test_few_long_reads():
@@ -43,8 +40,15 @@ def test_few_long_reads():
         plan, shaped = sd.Plan(offs, sd.I16), sd.Plan(offs, sd.I16)
         c = shaped.config
         shaped.set_config(c["strip"], c["chains"], c["waves_per_cu"], c["bands"])
-        want, _ = fastest(lambda: sd.align_batch(ref, shaped, qd))
-        got, (cost, end) = fastest(lambda: sd.align_batch(ref, plan, qd))
+        # The mean of calls in turn after one of each: the launch with 64 long reads takes
+        # 16 ms and, in about one call of twelve, 12, whichever plan it is, so that the
+        # fastest of a few calls may be either.
+        wants, gots = [], []
+        for _ in range(49):
+            wants.append(timed(lambda: sd.align_batch(ref, shaped, qd))[0])
+            t, (cost, end) = timed(lambda: sd.align_batch(ref, plan, qd))
+            gots.append(t)
+        want, got = np.mean(wants[1:]), np.mean(gots[1:])
         print(f"{lens.count(4096)} reads of 4,096 rows with {lens.count(lens[-1])} of "
               f"{lens[-1]}: {got:.2f} ms, {want:.2f} in one launch", flush=True)
         sys.stdout.flush()
@@ -53,9 +57,7 @@ def test_few_long_reads():
                 oracle.sdtw_i64(q[offs[i]:offs[i + 1]], ref_np)
         plan.close()
         shaped.close()
-        # (64 long reads on 256 CUs: one launch takes 12.0 or 15.7 ms, by where its
-        # workgroups land, so its time says nothing here)
-        assert got < 8 / 7 * want or lens.count(4096) > 1
+        assert got < 8 / 7 * want
     ref.close()
 
 
